@@ -21,15 +21,17 @@
 // query's keys needs one exchange across the four lane groups; the row sum is
 // one more MFMA per chunk with A = all ones.
 //
-// Data movement.  One workgroup owns NW x QW x 16 queries of one head and walks
-// the keys in steps of BKV (128).  K and V tiles ([BKV keys][d], row-major) share an
-// NS-slot ring in LDS filled by global->LDS copies of whole KiB (one barrier
-// per step); 16-byte pieces are XOR-swizzled per key row so that the K
-// fragment reads (16 rows at one piece) and the transposing V^T reads
-// (ds_read_b64_tr_b16) are free of bank conflicts.  Causal: key steps wholly
-// above the workgroup's queries are never read; a wave skips the products of
-// steps wholly above its own queries; keys above the diagonal inside a step
-// are masked to -inf before the exponentials.
+// Data movement.  K and V tiles ([keys][d], row-major) go through rings in LDS filled by
+// global->LDS copies of whole KiB; 16-byte pieces are XOR-swizzled per key row so that the K
+// fragment reads (16 rows at one piece) and the transposing V^T reads (ds_read_b64_tr_b16)
+// are free of bank conflicts.  Causal: key steps wholly above the workgroup's queries are
+// never read; a wave skips the products of steps wholly above its own queries; keys above
+// the diagonal inside a step are masked to -inf before the exponentials.
+//
+// Prefill (attention_prefill_kernel).  Bound by the matrix cores and by the power they and
+// the exponentials draw: causal 32 x 8192, d = 128 runs the pipe 65-68 % busy at 1.6-1.74 GHz
+// (55 % at 2.0 GHz before the two halves of a workgroup ran out of phase), 473 us against
+// 521 us in one run; 4096 keys without a mask 221 us against 239 us.
 //
 // Decode (a few new queries against a long key/value cache).  One workgroup
 // per head would leave most CUs idle, so the keys of each head are cut into
@@ -39,6 +41,7 @@
 // postponed once more, past the reduction over key ranges.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "dn_device.hpp"
 #include "dn_launch.hpp"
@@ -57,6 +60,12 @@ __device__ __forceinline__ void block_barrier() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+}
+// v_max3_f32 directly; the caller keeps matrix and transcendental results at a distance.
+__device__ __forceinline__ float max3f(float a, float b, float c) {
+    float d;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
 }
 // K rows: the A-operand read takes 16 consecutive rows at one 16-byte piece.
 // 256-byte rows span all 64 banks, so each of the 16 rows gets its own slot;
@@ -364,14 +373,456 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(const __bf16* __rest
     }
 }
 
-template <int D, int NW, int QW, int NS, int BKV>
+// Prefill.  NQW x QW x 16 queries per workgroup; KSP groups of NQW waves walk KSP
+// contiguous runs of the key steps, each through its own K and V rings (two slots each),
+// and their partial sums are merged in LDS at the end (Eq. (8) over key ranges).
+//
+// Schedule.  The eight waves sit two to a SIMD.  A step is an exponential phase (mask,
+// maximum, numerators, rare rescale: VALU) and a matrix phase (the products of this step
+// and the scores of the next: MFMA and LDS reads); the two halves of the workgroup run one
+// phase apart, separated by barriers, so that on every SIMD one wave's exponentials run
+// beside the other's matrix instructions.
+template <int D, int NQW, int QW, int KSP, int BKV>
+__global__ __launch_bounds__(NQW* KSP * 64) void attention_prefill_kernel(
+    const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V, int64_t Lq, int64_t Lk,
+    int causal, float sl2, int nqb, __bf16* __restrict__ out, int group) {
+    using namespace fa;
+    constexpr int NW = NQW * KSP;
+    constexpr int BQ = NQW * QW * 16;  // queries per workgroup
+    constexpr int NKB = BKV / 16;      // 16-key S^T blocks per step
+    constexpr int NKC = BKV / 32;      // 32-key chunks of the P.V product per step
+    constexpr int ROW = D * 2;         // bytes per K or V row
+    constexpr int TILE = BKV * ROW;    // one K (or V) slot
+    constexpr int RING = 4 * TILE;     // a key group's rings: K slots 0, 1, V slots 0, 1
+    constexpr int CW = NQW < NW / 2 ? NQW : NW / 2;  // late waves that share a tile's copies
+    constexpr int NG = KSP * CW / (NW / 2);          // key groups whose tiles a late wave copies
+    constexpr int T_INS = TILE / kChunkBytes / CW;   // copies per late wave per tile
+    constexpr int PPR = ROW / 16;      // 16-byte pieces per row
+    constexpr int RPI = kChunkBytes / ROW;  // rows per copy instruction
+    constexpr int DB = D / 16, DC = D / 32;
+    static_assert(TILE % (kChunkBytes * CW) == 0 && KSP % NG == 0, "copies split evenly over the late waves");
+    static_assert(NW % 2 == 0, "two halves");
+    constexpr int XCH = (KSP - 1) * NQW * 64 * QW * (DB + 1) * 16;  // merge exchange
+    constexpr int SMEM = KSP * RING > XCH ? KSP * RING : XCH;
+
+    __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int qg = wave % NQW, kg = wave / NQW;
+    const bool late = wave >= NW / 2;  // the half that runs one phase behind
+    // causal: all heads' longest query blocks first; else whole heads in a row on each XCD
+    int h, qb;
+    if (causal) {
+        longest_first(blockIdx.x, nqb, gridDim.x / nqb, h, qb);
+    } else {
+        const int t = xcd_contiguous(blockIdx.x, gridDim.x);
+        h = t / nqb;
+        qb = t % nqb;
+    }
+    const int64_t q0 = (int64_t)qb * BQ;
+    const int kv_end = (int)(causal ? min(Lk, q0 + BQ) : Lk);
+    // every group walks nsteps steps from its first key on; steps past kv_end are masked
+    const int nsteps = ((kv_end + BKV - 1) / BKV + KSP - 1) / KSP;
+    const int k_lo = kg * nsteps * BKV;
+
+    const __bf16* Qh = Q + (int64_t)h * Lq * D;
+    // grouped-query attention: query head h reads key/value head h / group
+    const __bf16* Kh = K + (int64_t)(h / group) * Lk * D;
+    const __bf16* Vh = V + (int64_t)(h / group) * Lk * D;
+    __bf16* Oh = out + (int64_t)h * Lq * D;
+
+    const int qw0 = (int)q0 + qg * QW * 16;  // first query of this wave (positions fit 32 bits)
+    const int G = lane >> 4, i = lane & 15;
+    int qrow[QW];
+#pragma unroll
+    for (int f = 0; f < QW; ++f) qrow[f] = qw0 + f * 16 + i;
+
+    // ---- K/V rings.  The late half issues every copy, at the start of its exponential phase,
+    // which has issue slots to spare; each of its waves copies T_INS KiB of the K and V tiles
+    // of NG key groups.  Copy instruction j covers tile rows RPI * (cw + j * CW) ..; lane l
+    // fetches piece (l % PPR) ^ swz(row), so logical piece p of a row lands in slot p ^ swz(row)
+    // (the swizzles repeat every 16 rows, PJ instructions).  Keys past Lk clamp onto the last
+    // row (their scores are masked); byte offsets from the head's base fit 32 bits
+    // (Lk * d * 2 < 2^31).
+    constexpr int PJ = CW * RPI >= 16 ? 1 : 16 / (CW * RPI);
+    const int cw = wave % CW, cg = kg % (KSP / NG);  // this wave's share of a tile, its first key group
+    const int c_row = cw * RPI + lane / PPR;
+    uint32_t k_off[PJ], v_off_g[PJ];
+#pragma unroll
+    for (int j = 0; j < PJ; ++j) {
+        const int r = c_row + j * CW * RPI;
+        k_off[j] = (uint32_t)(c_row * ROW + ((lane % PPR) ^ k_swz<D>(r)) * 16);
+        v_off_g[j] = (uint32_t)(c_row * ROW + ((lane % PPR) ^ v_swz<D>(r)) * 16);
+    }
+    const uint64_t k_base = uniform_u64(Kh), v_base = uniform_u64(Vh);
+    const uint32_t smem_addr = lds_addr32(smem);
+    // K (which = 0) or V (which = 1) of `step` of the wave's key groups
+    auto issue = [&](int which, int step) __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int gg = cg + g * (KSP / NG);
+            const uint32_t base = smem_addr + (uint32_t)(gg * RING + (2 * which + (step & 1)) * TILE + cw * kChunkBytes);
+            const uint32_t k0 = (uint32_t)((gg * nsteps + step) * BKV);
+            if (k0 + BKV <= (uint32_t)Lk) {  // no row to clamp: the step's offset goes into the scalar base
+                const uint64_t src = (which ? v_base : k_base) + (uint64_t)k0 * ROW;
+#pragma unroll
+                for (int j = 0; j < T_INS; ++j)
+                    g2lds16_async_sb(src + (uint64_t)(j * CW * kChunkBytes), which ? v_off_g[j % PJ] : k_off[j % PJ],
+                                     base + (uint32_t)(j * CW * kChunkBytes));
+            } else {
+                const uint32_t last = (uint32_t)(Lk - 1);
+#pragma unroll
+                for (int j = 0; j < T_INS; ++j) {
+                    const uint32_t piece = (which ? v_off_g[j % PJ] : k_off[j % PJ]) - (uint32_t)(c_row * ROW);
+                    const uint32_t row = k0 + (uint32_t)(c_row + j * CW * RPI);
+                    const uint32_t key = row < last ? row : last;  // a select, no branch
+                    g2lds16_async_sb(which ? v_base : k_base, key * (uint32_t)ROW + piece,
+                                     base + (uint32_t)(j * CW * kChunkBytes));
+                }
+            }
+        }
+    };
+    if (late) {
+        issue(0, 0);
+        issue(0, 1);
+        issue(1, 0);
+    }
+
+    // Q^T fragments (B operand of S^T): lane (i, G) holds query 16f + i, d 32c + 8G .. +8.
+    // The empty statements make the compiler place its waits for these loads here and not
+    // inside the key loop, where they would also drain the copies in flight.
+    u32x4 qf[QW][DC];
+#pragma unroll
+    for (int f = 0; f < QW; ++f) {
+        const int64_t qr = qrow[f] < Lq ? qrow[f] : Lq - 1;
+#pragma unroll
+        for (int c = 0; c < DC; ++c) qf[f][c] = ld16(Qh + qr * D + 32 * c + 8 * G);
+    }
+#pragma unroll
+    for (int f = 0; f < QW; ++f)
+#pragma unroll
+        for (int c = 0; c < DC; ++c) asm volatile("" : "+v"(qf[f][c]));
+
+    // Lane-constant LDS offsets, as in attention_kernel.
+    int k_rd[DC];
+#pragma unroll
+    for (int c = 0; c < DC; ++c) k_rd[c] = i * ROW + (((4 * c + G) ^ k_swz<D>(i)) << 4);
+    const int vr = 4 * G + (i >> 2);
+    const int vsw2 = v_swz<D>(vr) >> 1;  // swizzle of the 32-byte d block
+    int v_off[DB];
+#pragma unroll
+    for (int b = 0; b < DB; ++b) v_off[b] = vr * ROW + (i & 3) * 8 + 32 * (b ^ vsw2);
+
+    f32x4 acc[QW][DB], accl[QW];
+#pragma unroll
+    for (int f = 0; f < QW; ++f) {
+#pragma unroll
+        for (int b = 0; b < DB; ++b) acc[f][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        accl[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+    // Reference maximum per query in scaled log2 units, raised only when a step exceeds it
+    // by more than 8 (numerators stay below 256; the rescale, an exact identity, is rare).
+    float mref[QW];
+#pragma unroll
+    for (int f = 0; f < QW; ++f) mref[f] = -__builtin_inff();
+
+    // the wave's steps: those not wholly above its queries
+    const int qlast = qw0 + QW * 16 - 1;
+    const int n_w = causal ? (qlast >= k_lo ? min(nsteps, (qlast - k_lo) / BKV + 1) : 0) : nsteps;
+    const char* kring = smem + kg * RING;
+    const char* vring = kring + 2 * TILE;
+
+    f32x4 st[QW][NKB];  // scores S^T of one step
+    u32x4 pf[QW][NKC];  // numerators of one step, bf16
+
+    // Matrix phase.  The fragments are read from LDS one group ahead of their products --
+    // a 32-key chunk of V^T (2 DB transposing reads) beside the products of the chunk before,
+    // a pair of K blocks (2 DC reads) beside the pair before -- in an order fixed by scheduling
+    // groups: left to itself the compiler reads two MFMAs ahead, less than the LDS latency,
+    // and with one wave per SIMD in this phase nothing else covers it.
+    auto read_v = [&](const char* vb, int kc, u32x4(&vf)[DB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < DB; ++b) {
+            const uint2 lo = lds_tr16(vb + v_off[b] + (kc * 32) * ROW);
+            const uint2 hi = lds_tr16(vb + v_off[b] + (kc * 32 + 16) * ROW);
+            vf[b] = u32x4{lo.x, lo.y, hi.x, hi.y};
+        }
+    };
+    auto read_k = [&](const char* kb, int j, u32x4(&kf)[2][DC]) __attribute__((always_inline)) {  // key blocks 2j, 2j + 1
+#pragma unroll
+        for (int c = 0; c < DC; ++c)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) kf[b][c] = lds_ld16(lds_ptr((char*)kb + (2 * j + b) * 16 * ROW + k_rd[c]));
+    };
+    constexpr int kSgMfma = 0x008, kSgDsRead = 0x100;
+    // out^T += V^T . P~^T of `step` (if PV), then S^T = K . Q^T of step + 1 (if QK)
+    auto matrix = [&](int step, auto do_pv, auto do_qk) __attribute__((always_inline)) {
+        constexpr bool PV = decltype(do_pv)::value, QK = decltype(do_qk)::value;
+        const char* vb = vring + (step & 1) * TILE;
+        const char* kb = kring + ((step + 1) & 1) * TILE;
+        u32x4 vf[2][DB], kf[2][2][DC];
+        if constexpr (PV) {
+            read_v(vb, 0, vf[0]);
+            // the row sums need no fragment from LDS: they cover the latency of the first reads
+#pragma unroll
+            for (int kc = 0; kc < NKC; ++kc)
+#pragma unroll
+                for (int f = 0; f < QW; ++f) accl[f] = mfma_chunk<__bf16>(ones, pf[f][kc], accl[f]);
+#pragma unroll
+            for (int kc = 0; kc < NKC; ++kc) {
+                if (kc + 1 < NKC) read_v(vb, kc + 1, vf[(kc + 1) & 1]);
+                if (QK && kc + 1 == NKC) read_k(kb, 0, kf[0]);
+#pragma unroll
+                for (int b = 0; b < DB; ++b)
+#pragma unroll
+                    for (int f = 0; f < QW; ++f) acc[f][b] = mfma_chunk<__bf16>(vf[kc & 1][b], pf[f][kc], acc[f][b]);
+            }
+        } else {
+            read_k(kb, 0, kf[0]);
+        }
+        if constexpr (QK) {
+#pragma unroll
+            for (int f = 0; f < QW; ++f)
+#pragma unroll
+                for (int b4 = 0; b4 < NKB; ++b4) st[f][b4] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < NKC; ++j) {
+                if (j + 1 < NKC) read_k(kb, j + 1, kf[(j + 1) & 1]);
+#pragma unroll
+                for (int c = 0; c < DC; ++c)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int f = 0; f < QW; ++f)
+                            st[f][2 * j + b] = mfma_chunk<__bf16>(kf[j & 1][b][c], qf[f][c], st[f][2 * j + b]);
+            }
+        }
+        // the order of the reads and products above
+        if constexpr (PV) {
+            __builtin_amdgcn_sched_group_barrier(kSgDsRead, 2 * DB, 0);
+            __builtin_amdgcn_sched_group_barrier(kSgMfma, NKC * QW, 0);
+#pragma unroll
+            for (int kc = 0; kc < NKC; ++kc) {
+                constexpr int NM = QW * DB;
+                const int nd = kc + 1 < NKC ? 2 * DB : (QK ? 2 * DC : 0);
+#pragma unroll
+                for (int m = 0; m < NM; ++m) {
+                    __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 0);
+                    const int r = nd * (m + 1) / NM - nd * m / NM;
+                    if (r == 1) __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
+                    if (r == 2) __builtin_amdgcn_sched_group_barrier(kSgDsRead, 2, 0);
+                }
+            }
+        } else {
+            __builtin_amdgcn_sched_group_barrier(kSgDsRead, 2 * DC, 0);
+        }
+        if constexpr (QK) {
+#pragma unroll
+            for (int j = 0; j < NKC; ++j) {
+                constexpr int NM = QW * 2 * DC;
+                const int nd = j + 1 < NKC ? 2 * DC : 0;
+#pragma unroll
+                for (int m = 0; m < NM; ++m) {
+                    __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 0);
+                    const int r = nd * (m + 1) / NM - nd * m / NM;
+                    if (r == 1) __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
+                }
+            }
+        }
+    };
+    auto numerators = [&](int step) __attribute__((always_inline)) {
+        const int k0 = k_lo + step * BKV;
+        if ((causal && k0 + BKV - 1 > qw0) || k0 + BKV > kv_end) {
+#pragma unroll
+            for (int f = 0; f < QW; ++f) {
+                const int lim = causal ? min(qrow[f], kv_end - 1) : kv_end - 1;
+#pragma unroll
+                for (int b4 = 0; b4 < NKB; ++b4) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (k0 + 16 * b4 + 4 * G + e > lim) st[f][b4][e] = -__builtin_inff();
+                    // one block's compare masks at a time: issued all at once they
+                    // took 64 SGPRs and pushed loop-long scalars into VGPR lanes
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+        // The maxima go through v_max3_f32 in inline assembly (fmaxf on matrix results gets an
+        // extra canonicalizing max per operand), which the compiler's hazard pass does not
+        // guard: 20 wait states cover the longest matrix-result-to-VALU distance.
+#pragma unroll
+        for (int f = 0; f < QW; ++f)
+#pragma unroll
+            for (int b4 = 0; b4 < NKB; ++b4) {
+                if (f == 0 && b4 == 0)
+                    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(st[f][b4]));
+                else
+                    asm volatile("" : "+v"(st[f][b4]));
+            }
+        float tmax[QW];
+        bool want = false;
+#pragma unroll
+        for (int f = 0; f < QW; ++f) {
+            float m2[NKB];
+#pragma unroll
+            for (int b4 = 0; b4 < NKB; ++b4)
+                m2[b4] = max3f(max3f(st[f][b4][0], st[f][b4][1], st[f][b4][2]), st[f][b4][3],
+                               b4 >= NKB / 2 ? m2[b4 - NKB / 2] : st[f][b4][3]);
+            tmax[f] = m2[NKB / 2];
+#pragma unroll
+            for (int b4 = NKB / 2 + 1; b4 + 1 < NKB; b4 += 2) tmax[f] = max3f(tmax[f], m2[b4], m2[b4 + 1]);
+            if constexpr (NKB / 2 % 2 == 0) tmax[f] = max3f(tmax[f], m2[NKB - 1], m2[NKB - 1]);
+            want |= tmax[f] * sl2 > mref[f] + 8.0f;
+        }
+        // a query's reference rises exactly when one of its four lanes' own maxima exceeds it
+        // by more than 8 (the scale is positive), so the cross-lane maximum is formed, and the
+        // partial sums rescaled, only in the rare steps where some lane asks for it
+        if (__any(want)) {
+#pragma unroll
+            for (int f = 0; f < QW; ++f) {
+                const float tmax2 = max_lane_groups(tmax[f]) * sl2;
+                const bool raise = tmax2 > mref[f] + 8.0f;
+                const float mnew = raise ? tmax2 : mref[f];
+                const float alpha = __builtin_amdgcn_exp2f(raise ? mref[f] - mnew : 0.f);
+                mref[f] = mnew;
+#pragma unroll
+                for (int b = 0; b < DB; ++b) acc[f][b] *= alpha;
+                accl[f] *= alpha;
+            }
+        }
+#pragma unroll
+        for (int f = 0; f < QW; ++f) {
+            const float nb = mref[f] == -__builtin_inff() ? 0.f : -mref[f];
+            float p[NKB][4];
+#pragma unroll
+            for (int b4 = 0; b4 < NKB; ++b4)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) p[b4][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[f][b4][e], sl2, nb));
+#pragma unroll
+            for (int kc = 0; kc < NKC; ++kc)
+                pf[f][kc] = u32x4{pack_bf16(p[2 * kc][0], p[2 * kc][1]), pack_bf16(p[2 * kc][2], p[2 * kc][3]),
+                                  pack_bf16(p[2 * kc + 1][0], p[2 * kc + 1][1]),
+                                  pack_bf16(p[2 * kc + 1][2], p[2 * kc + 1][3])};
+        }
+    };
+    // Phases: the early half runs the exponentials of step s in phase 2s and its matrix work
+    // in phase 2s + 1, the late half one phase later.  K(s+1) and V(s) are read in phases
+    // 2s + 1 and 2s + 2; their slots take K(s+3) and V(s+2), issued in phase 2s + 3 and
+    // waited for (each wave its own copies) before the barrier that ends phase 2s + 4.
+    wait_vmcnt_asm<0>();
+    block_barrier();
+    if (late) block_barrier();
+    using yes = std::true_type;
+    using no = std::false_type;
+    if (n_w > 0) matrix(-1, no{}, yes{});
+    wait_lgkm0();
+    block_barrier();
+    auto step = [&](int s, auto work, auto next) __attribute__((always_inline)) {  // work: the wave's own step; next: not its last
+        if (late) {
+            issue(0, s + 2);
+            issue(1, s + 1);
+        }
+        if constexpr (decltype(work)::value) {
+            numerators(s);
+            // used here, so that the exponentials are not sunk past the barrier
+#pragma unroll
+            for (int f = 0; f < QW; ++f)
+#pragma unroll
+                for (int kc = 0; kc < NKC; ++kc) asm volatile("" : "+v"(pf[f][kc]));
+        }
+        block_barrier();
+        if constexpr (decltype(work)::value) {
+            __builtin_amdgcn_s_setprio(1);
+            matrix(s, yes{}, next);
+            __builtin_amdgcn_s_setprio(0);
+        }
+        if (late) wait_vmcnt_asm<0>();
+        wait_lgkm0();
+        block_barrier();
+    };
+    int s = 0;
+    for (; s < n_w - 1; ++s) step(s, yes{}, yes{});
+    if (s < n_w) {
+        step(s, yes{}, no{});
+        ++s;
+    }
+    for (; s < nsteps; ++s) step(s, no{}, no{});
+    if (!late) block_barrier();
+    wait_vmcnt_asm<0>();  // no copy into LDS may outlive the workgroup
+
+    if constexpr (KSP > 1) {
+        // Merge: groups 1 .. leave (acc, l, m) in LDS (the rings are idle now), group 0
+        // rescales everything to the largest reference.  A group without any unmasked key
+        // has m = -inf and contributes nothing.
+        f32x4* xch = reinterpret_cast<f32x4*>(smem);
+        block_barrier();  // every wave's copies have landed
+        if (kg > 0) {
+#pragma unroll
+            for (int f = 0; f < QW; ++f) {
+                f32x4* x = xch + (((kg - 1) * NQW + qg) * QW + f) * (DB + 1) * 64 + lane;
+#pragma unroll
+                for (int b = 0; b < DB; ++b) x[b * 64] = acc[f][b];
+                x[DB * 64] = f32x4{accl[f][0], mref[f], 0.f, 0.f};
+            }
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int f = 0; f < QW; ++f) {
+            float m = mref[f];
+            float lg[KSP], mg[KSP];
+#pragma unroll
+            for (int g = 1; g < KSP; ++g) {
+                const f32x4 lm = xch[((((g - 1) * NQW + qg) * QW + f) * (DB + 1) + DB) * 64 + lane];
+                lg[g] = lm[0];
+                mg[g] = lm[1];
+                m = mg[g] > m ? mg[g] : m;
+            }
+            const float a0 = mref[f] == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(mref[f] - m);
+#pragma unroll
+            for (int b = 0; b < DB; ++b) acc[f][b] *= a0;
+            accl[f][0] *= a0;
+#pragma unroll
+            for (int g = 1; g < KSP; ++g) {
+                const float ag = mg[g] == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(mg[g] - m);
+                const f32x4* x = xch + (((g - 1) * NQW + qg) * QW + f) * (DB + 1) * 64 + lane;
+#pragma unroll
+                for (int b = 0; b < DB; ++b) {
+                    const f32x4 v = x[b * 64];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[f][b][e] = __builtin_fmaf(v[e], ag, acc[f][b][e]);
+                }
+                accl[f][0] = __builtin_fmaf(lg[g], ag, accl[f][0]);
+            }
+        }
+    }
+
+    // ---- epilogue: the single deferred division, one rounding to bf16
+#pragma unroll
+    for (int f = 0; f < QW; ++f) {
+        if (qrow[f] >= Lq) continue;
+        const float inv = 1.0f / accl[f][0];
+        __bf16* orow = Oh + (int64_t)qrow[f] * D + 4 * G;
+#pragma unroll
+        for (int b = 0; b < DB; ++b) {
+            uint2 v;
+            v.x = pack_bf16(acc[f][b][0] * inv, acc[f][b][1] * inv);
+            v.y = pack_bf16(acc[f][b][2] * inv, acc[f][b][3] * inv);
+            *reinterpret_cast<uint2*>(orow + b * 16) = v;
+        }
+    }
+}
+
+template <int D, int NQW, int QW, int KSP, int BKV>
 static hipError_t run_attention(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq, int64_t Lk,
                                 int causal, float scale, void* out, hipStream_t s, int group) {
-    constexpr int BQ = NW * QW * 16;
+    constexpr int BQ = NQW * QW * 16;
     const int nqb = (int)((Lq + BQ - 1) / BQ);
-    attention_kernel<D, NW, QW, NS, BKV><<<dim3((unsigned)(BH * nqb)), NW * 64, 0, s>>>(
-        (const __bf16*)Q, (const __bf16*)K, (const __bf16*)V, Lq, Lk, causal, scale * fa::kLog2e, nqb, 1, Lk,
-        nullptr, (__bf16*)out, group);
+    attention_prefill_kernel<D, NQW, QW, KSP, BKV><<<dim3((unsigned)(BH * nqb)), NQW * KSP * 64, 0, s>>>(
+        (const __bf16*)Q, (const __bf16*)K, (const __bf16*)V, Lq, Lk, causal, scale * fa::kLog2e, nqb,
+        (__bf16*)out, group);
     return hipGetLastError();
 }
 
@@ -504,14 +955,58 @@ hipError_t launch_attention_decode_noalloc(const void* Q, const void* K, const v
     return launch_attention_decode(Q, K, V, BH, Lq, Lk, d, scale, part, out, s);
 }
 
+// Query rows per workgroup of the prefill layouts (every layout's key step covers 128 keys).
+constexpr int64_t kMaxPrefillGrid = (int64_t(1) << 31) - 1;
+constexpr int kPrefillBQ[4] = {256, 128, 64, 32};
+
+// Which layout.  Fewer queries per workgroup cost more per score (the K and V fragments read
+// from LDS serve fewer queries: per 128-key step at d = 128 and a full chip 3.35 us for 256
+// queries, 1.9 for 128, 1.3 for 64, 1.0 for 32), but give more workgroups and split each one's
+// keys 1, 2, 4 and 4 ways.  The time is about the larger of the longest workgroup's (its steps
+// at the lone-workgroup rate, plus a start and an end) and of all the work over 256 CUs; the
+// layout with the smallest estimate runs.  Measured, best layout against 256 queries for all
+// (graph replays, us): 8 heads x 512, d64 7.2 / 14; 32 x 1000 causal 20.9 / 29; 16 x 512
+// against 3000 keys 27 / 67; 32 x 2048 causal 45 / 51; from 32 x 4096 causal on 256 is best
+// (122 / 142 with 128).
+static int prefill_layout(int64_t BH, int64_t Lq, int64_t Lk, int64_t d, int causal) {
+    struct Cost {
+        double full, alone, ends;  // us per step with every CU busy / alone, us per workgroup
+    };
+    static constexpr Cost kCost[2][4] = {{{2.0, 1.75, 7.0}, {1.2, 1.1, 6.0}, {0.64, 0.7, 3.5}, {0.44, 0.5, 2.8}},
+                                         {{3.35, 2.5, 8.0}, {1.9, 1.55, 6.5}, {1.3, 1.1, 6.0}, {1.0, 0.88, 3.5}}};
+    int best = 0;
+    double best_t = 0;
+    for (int v = 0; v < 4; ++v) {
+        const Cost& c = kCost[d == 128][v];
+        const int64_t n = (Lq + kPrefillBQ[v] - 1) / kPrefillBQ[v], wgs = BH * n;
+        if (wgs > kMaxPrefillGrid) continue;
+        const int64_t longest = (Lk + 127) / 128;
+        const double mean = causal ? 0.5 * (double)(longest + 1) : (double)longest;
+        const double t = std::max((double)longest * c.alone + c.ends, (double)wgs * (mean * c.full + c.ends) / 256.0);
+        if (v == 0 || t < best_t) {
+            best = v;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
+template <int D>
+static hipError_t run_prefill(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq, int64_t Lk,
+                              int causal, float scale, void* out, hipStream_t s, int group) {
+    switch (prefill_layout(BH, Lq, Lk, D, causal)) {
+        case 0: return run_attention<D, 8, 2, 1, 128>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
+        case 1: return run_attention<D, 4, 2, 2, 64>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
+        case 2: return run_attention<D, 2, 2, 4, 32>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
+        default: return run_attention<D, 2, 1, 4, 32>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
+    }
+}
+
 hipError_t launch_attention_deferred(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq,
                                      int64_t Lk, int64_t d, int causal, float scale, void* out, hipStream_t s,
-                                     int group) {
-    // 8 waves x 2 query fragments (256 queries per workgroup), two ring slots of 128 keys
-    // (128 KiB of LDS at d = 128): measured fastest against 64-key steps, 3 slots, 1 or 3
-    // fragments, and 4 waves on the causal 32 x 8192 x 8192, d = 128.  BH counts query heads.
-    if (d == 64) return run_attention<64, 8, 2, 2, 128>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
-    return run_attention<128, 8, 2, 2, 128>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
+                                     int group) {  // BH counts query heads
+    if (d == 64) return run_prefill<64>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
+    return run_prefill<128>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
 }
 
 }  // namespace dn

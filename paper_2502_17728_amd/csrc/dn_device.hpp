@@ -249,4 +249,16 @@ __device__ __forceinline__ int xcd_contiguous(int bid, int nblk) {
     return x * q + (x < r ? x : r) + local;
 }
 
+
+// Causal grids of nq query blocks x nh heads, whose work grows with the query block: all
+// heads' longest blocks first.  The dispatcher deals workgroups in order to the XCDs and, in
+// each, to the shader engines, so with each head's blocks in a row the long blocks of one
+// engine pile up; in this order every engine gets the same mix.  Where the heads divide among
+// the 8 XCDs each XCD keeps a contiguous range of heads (keys and values under one L2).
+__device__ __forceinline__ void longest_first(int bid, int nq, int nh, int& head, int& qb) {
+    const int r = bid / nh, c = bid - r * nh;
+    head = nh % 8 == 0 ? (c & 7) * (nh >> 3) + (c >> 3) : c;
+    qb = nq - 1 - r;
+}
+
 }  // namespace dn

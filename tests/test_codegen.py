@@ -88,3 +88,8 @@ def test_key_loops_carry_only_hand_counted_waits(src, prefix):
             waits = _compiler_vmcnt_waits(body, a, b)
             assert not waits, f"{name}: compiler-placed vmcnt waits inside a key loop: {waits}"
     assert seen > 0
+
+
+def test_prefill_key_loops_carry_only_hand_counted_waits():
+    # the prefill kernel's loops, by the same rule
+    test_key_loops_carry_only_hand_counted_waits("attention.hip", "_ZN2dn24attention_prefill_kernel")
