@@ -50,16 +50,10 @@ namespace dn {
 namespace fa {
 constexpr float kLog2e = 1.4426950408889634f;
 
-__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4)); }
 template <int N>
 __device__ __forceinline__ void wait_vmcnt_asm() {
     static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ void block_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
 }
 // v_max3_f32 directly; the caller keeps matrix and transcendental results at a distance.
 __device__ __forceinline__ float max3f(float a, float b, float c) {
@@ -556,7 +550,6 @@ __global__ __launch_bounds__(NQW* KSP * 64) void attention_prefill_kernel(
 #pragma unroll
             for (int b = 0; b < 2; ++b) kf[b][c] = lds_ld16(lds_ptr((char*)kb + (2 * j + b) * 16 * ROW + k_rd[c]));
     };
-    constexpr int kSgMfma = 0x008, kSgDsRead = 0x100;
     // out^T += V^T . P~^T of `step` (if PV), then S^T = K . Q^T of step + 1 (if QK)
     auto matrix = [&](int step, auto do_pv, auto do_qk) __attribute__((always_inline)) {
         constexpr bool PV = decltype(do_pv)::value, QK = decltype(do_qk)::value;

@@ -261,4 +261,37 @@ __device__ __forceinline__ void longest_first(int bid, int nq, int nh, int& head
     qb = nq - 1 - r;
 }
 
+// ----------------------------------------------------------------- LayerNorm/RMSNorm products
+// SiLU(z) = z / (1 + e^-z) with e^-z = 2^(-z log2 e) on the hardware exponential;
+// below z ~ -88 that overflows to +inf and the quotient is -0, the limit.
+constexpr float kLog2eF = 1.4426950408889634f;
+__device__ __forceinline__ float silu(float z) { return z / (1.0f + __builtin_amdgcn_exp2f(-z * kLog2eF)); }
+
+// Address of packed chunk (nb, kc), lane `lane` (bytes from the packed base).
+__device__ __forceinline__ int64_t packed_chunk(int64_t nb, int64_t kc, int64_t kchunks, int lane) {
+    return ((nb * kchunks + kc) * kWave + lane) * 16;
+}
+
+// Slot of 16-byte piece p of tile row r of x in LDS: p ^ a_swz(r).  Any 8 or 16 consecutive rows
+// read at one piece index hit distinct banks.
+__device__ __forceinline__ int a_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+
+// instruction classes of the scheduling groups
+constexpr int kSgValu = 0x002, kSgMfma = 0x008, kSgDsRead = 0x100;
+
+// ---------------------------------------------------------------------------- waits
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+    static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
+    // gfx9 s_waitcnt: vmcnt[3:0] bits 3:0, vmcnt[5:4] bits 15:14, expcnt bits 6:4, lgkmcnt bits 11:8
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4)); }
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void block_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 }  // namespace dn

@@ -43,6 +43,25 @@ hipError_t launch_ln_linear_deferred(const void* x, const void* packed, int64_t 
                                      int64_t N, int dtype, float eps, int rms, const float* row_stats,
                                      void* out, hipStream_t s, float* stats_out = nullptr);
 
+// Products of few rows (bf16, W' packed): row blocks of 32 .. 128 rows, both operands streamed
+// through LDS rings.  x below 2^31 bytes per row block (K < 2^22).  gated: N counts packed
+// columns and n_out the output features.  plain: no normalization, bias [N] (nullable).
+struct SkinnyArgs {
+    const void* x;
+    const void* W;  // packed chunks
+    const void* bias;
+    void* out;
+    int64_t M, K, N, n_out, kchunks, nblocks;
+    const float* c_col;
+    const float* b_col;
+    float eps;
+    int rms;
+    const float* row_stats;
+    float* stats_out;
+};
+hipError_t launch_skinny(const SkinnyArgs& a, bool gated, bool plain, hipStream_t s);
+double skinny_estimate_us(int64_t M, int64_t K, int64_t nblocks, bool gated);
+
 // y = (x - mean) rstd gamma + beta from per-row (mean, rstd); beta nullable.
 hipError_t launch_apply_norm(const void* x, const float* stats, const void* gamma, const void* beta, int64_t M,
                              int64_t K, int dtype, void* y, hipStream_t s);

@@ -67,31 +67,6 @@ struct MainArgs {
     uint32_t mom_wait_ticks;  // bound of the wait for the peers' shares, s_memrealtime ticks (100 MHz)
 };
 
-// SiLU(z) = z / (1 + e^-z) with e^-z = 2^(-z log2 e) on the hardware exponential;
-// below z ~ -88 that overflows to +inf and the quotient is -0, the limit.
-constexpr float kLog2eF = 1.4426950408889634f;
-__device__ __forceinline__ float silu(float z) { return z / (1.0f + __builtin_amdgcn_exp2f(-z * kLog2eF)); }
-
-// ---------------------------------------------------------------------------- waits
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
-    // gfx9 s_waitcnt: vmcnt[3:0] bits 3:0, vmcnt[5:4] bits 15:14, expcnt bits 6:4, lgkmcnt bits 11:8
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4)); }
-__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ void block_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-// Address of packed chunk (nb, kc), lane `lane` (bytes from the packed base).
-__device__ __forceinline__ int64_t packed_chunk(int64_t nb, int64_t kc, int64_t kchunks, int lane) {
-    return ((nb * kchunks + kc) * kWave + lane) * 16;
-}
-
 // =============================================================================
 // General main loop: 128x128 (bf16) or 32x64 (fp32) tiles.  Used for problems
 // too small for the 256x256 kernel, for K not a multiple of 64, for fp32, for
@@ -508,7 +483,6 @@ __global__ __launch_bounds__(WM* WN* kWave) void main_loop_kernel(MainArgs p) {
 // middle of stage s (when every wave has finished reading stage s), so it has
 // a whole stage of MFMA time to land.
 // =============================================================================
-constexpr int kSgValu = 0x002, kSgMfma = 0x008, kSgDsRead = 0x100;
 // cache-policy operand of the buffer stores: non-temporal
 constexpr int kStoreStream = 2;
 
@@ -521,8 +495,6 @@ __device__ __forceinline__ u32x4 normalize_chunk(const u32x4& a, float r, float 
         o[j] = pack_bf16(__builtin_fmaf(bf_lo(w[j]), r, nb), __builtin_fmaf(bf_hi(w[j]), r, nb));
     return u32x4{o[0], o[1], o[2], o[3]};
 }
-
-__device__ __forceinline__ int a_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
 template <Epi EPI, int WM, int WN, int BM = 256, int BN = 256>
 __global__ __launch_bounds__(WM* WN* kWave) void pipe_kernel(MainArgs p, int group) {
@@ -964,7 +936,7 @@ __global__ __launch_bounds__(WM* WN* kWave) void pipe_kernel(MainArgs p, int gro
 }
 
 // =============================================================================
-// Decode-shaped deferred LN -> Linear: M <= 128 tokens, bf16.
+// Decode-shaped deferred LN -> Linear: M <= 16 tokens, bf16.
 // The work is streaming W' from HBM.  Each workgroup owns NC blocks of 16
 // output columns and its KS waves split K; per 32-k chunk a wave reads the
 // (zero-padded) x fragment once and NC packed W' chunks straight from HBM into
@@ -978,7 +950,7 @@ __global__ __launch_bounds__(WM* WN* kWave) void pipe_kernel(MainArgs p, int gro
 // 2j+1 of the group form output block j), out[M][n_out] = SiLU(gate) * up.
 // PLAIN: the plain product out = x . W' + bias (bias: [N] bf16, nullable), no
 // moments -- the decode-shaped GEMM of the unfused comparators.
-template <int KS, int NC, int U, bool SW = false, bool PLAIN = false, int MT = 1>
+template <int KS, int NC, int U, bool SW = false, bool PLAIN = false>
 __global__ __launch_bounds__(KS * kWave) void ln_decode_bf16_kernel(const __bf16* __restrict__ x,
                                                              const char* __restrict__ Wp, int64_t kchunks,
                                                              int64_t nblocks, const float* __restrict__ c_col,
@@ -990,82 +962,62 @@ __global__ __launch_bounds__(KS * kWave) void ln_decode_bf16_kernel(const __bf16
                                                              const __bf16* __restrict__ bias) {
     static_assert(!SW || NC % 2 == 0, "gate/up block pairs");
     static_assert(!(SW && PLAIN), "the plain product has no gate");
-    // MT fragments of 16 token rows (M <= 16 MT), reduced one fragment at a time; the
-    // slots hold the fragment's moments (sum x, Gram) and then the NC column blocks'
-    // partial products
+    // the slots hold the rows' moments (sum x, Gram) and then the NC column blocks' partial
+    // products
     constexpr int SLOTS = 2 + NC;
     __shared__ f32x4 part[SLOTS][KS][kWave];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t nb0 = (int64_t)blockIdx.x * NC;
     const int row = lane & 15;
-    bool row_ok[MT];
-    const __bf16* xr[MT];
-#pragma unroll
-    for (int f = 0; f < MT; ++f) {
-        row_ok[f] = 16 * f + row < M;
-        xr[f] = x + (int64_t)(row_ok[f] ? 16 * f + row : 0) * K;
-    }
+    const bool row_ok = row < M;
+    const __bf16* xr = x + (int64_t)(row_ok ? row : 0) * K;
     const char* wr[NC];
 #pragma unroll
     for (int q = 0; q < NC; ++q) wr[q] = Wp + packed_chunk(min(nb0 + q, nblocks - 1), 0, kchunks, lane);
 
-    // The KS waves split the chunks: with one row fragment interleaved (wave w takes
-    // chunks w, w + KS, ..., so the waves of a workgroup read neighbouring KiB of each
-    // column block at a time), with more in contiguous ranges.  Measured: 1 token on
-    // 8192 -> 2 x 28672 (gated MLP) 152.5 -> 141.4 us and on 8192 -> 28672 78.1 ->
-    // 77.3 us interleaved; 32 tokens on 4096 -> 12288 25.2 -> 27.3 us, so ranges there.
-    constexpr bool ILV = MT == 1;
-    const int64_t nchunks = kchunks;
-    const int64_t per = (nchunks + KS - 1) / KS;
-    const int64_t c_begin = ILV ? 0 : wave * per;
-    const int64_t c_end = ILV ? (nchunks > wave ? (nchunks - wave + KS - 1) / KS : 0) : min(nchunks, c_begin + per);
+    // The KS waves split the chunks interleaved (wave w takes chunks w, w + KS, ..., so the
+    // waves of a workgroup read neighbouring KiB of each column block at a time).  Measured
+    // against contiguous ranges: 1 token on 8192 -> 2 x 28672 (gated MLP) 152.5 -> 141.4 us
+    // and on 8192 -> 28672 78.1 -> 77.3 us.
+    const int64_t c_end = kchunks > wave ? (kchunks - wave + KS - 1) / KS : 0;  // this wave's chunks
 
     const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
     const u32x4 zero = {0, 0, 0, 0};
     const f32x4 fz = {0.f, 0.f, 0.f, 0.f};
-    f32x4 acc[MT][NC], sx[MT], sxx[MT];
+    f32x4 acc[NC], sx = fz, sxx = fz;
 #pragma unroll
-    for (int f = 0; f < MT; ++f) {
-        sx[f] = sxx[f] = fz;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) acc[f][q] = fz;
-    }
+    for (int q = 0; q < NC; ++q) acc[q] = fz;
 
     // Software pipeline over groups of U chunks: the loads of group g + 1 are in
     // flight while group g multiplies.  Every load is unconditional (chunk
     // indexes clamp to the wave's last chunk, x reads past the range turn into
     // zeros) so the wait counts stay exact; the group count is rounded up to
     // even and a group wholly past the range adds x = 0 times finite W'.
-    const int64_t ngroups = c_end > c_begin ? (c_end - c_begin + U - 1) / U : 0;
-    u32x4 a0[U][MT], b0[U][NC], a1[U][MT], b1[U][NC];
-    auto load = [&](u32x4(&a)[U][MT], u32x4(&b)[U][NC], int64_t g) {
+    const int64_t ngroups = (c_end + U - 1) / U;
+    u32x4 a0[U], b0[U][NC], a1[U], b1[U][NC];
+    auto load = [&](u32x4(&a)[U], u32x4(&b)[U][NC], int64_t g) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t ci = c_begin + g * U + u;  // the wave's ci-th chunk
+            const int64_t ci = g * U + u;  // the wave's ci-th chunk
             const bool ok = ci < c_end;
-            const int64_t cl = ILV ? (ok ? ci : c_end - 1) * KS + wave : (ok ? ci : c_end - 1);
+            const int64_t cl = (ok ? ci : c_end - 1) * KS + wave;
             const int64_t kk = cl * 32 + (lane >> 4) * 8;
 #pragma unroll
             for (int q = 0; q < NC; ++q) b[u][q] = ld16_stream(wr[q] + cl * kWave * 16);  // zero-padded past K
-#pragma unroll
-            for (int f = 0; f < MT; ++f) {
-                const u32x4 xv = ld16(xr[f] + min(kk, K - 8));  // K % 8 == 0
-                a[u][f] = (ok && kk < K && row_ok[f]) ? xv : zero;
-            }
+            const u32x4 xv = ld16(xr + min(kk, K - 8));  // K % 8 == 0
+            a[u] = (ok && kk < K && row_ok) ? xv : zero;
         }
     };
-    auto compute = [&](const u32x4(&a)[U][MT], const u32x4(&b)[U][NC]) {
+    auto compute = [&](const u32x4(&a)[U], const u32x4(&b)[U][NC]) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
 #pragma unroll
-            for (int f = 0; f < MT; ++f) {
-#pragma unroll
-                for (int q = 0; q < NC; ++q) acc[f][q] = mfma_chunk<__bf16>(a[u][f], b[u][q], acc[f][q]);
-                if constexpr (!PLAIN) {
-                    sx[f] = mfma_chunk<__bf16>(a[u][f], ones, sx[f]);
-                    sxx[f] = mfma_chunk<__bf16>(a[u][f], a[u][f], sxx[f]);
-                }
+            for (int q = 0; q < NC; ++q) acc[q] = mfma_chunk<__bf16>(a[u], b[u][q], acc[q]);
+            if constexpr (!PLAIN) {
+                sx = mfma_chunk<__bf16>(a[u], ones, sx);
+                sxx = mfma_chunk<__bf16>(a[u], a[u], sxx);
             }
+        }
     };
     if (ngroups > 0) {
         load(a0, b0, 0);
@@ -1076,65 +1028,60 @@ __global__ __launch_bounds__(KS * kWave) void ln_decode_bf16_kernel(const __bf16
             compute(a1, b1);
         }
     }
-    // Row fragment f and column block j of the workgroup (SW: block pair j, gate
-    // then up): reduce over the KS slices of K, then the epilogue.
+    // Column block j of the workgroup (SW: block pair j, gate then up): reduce over the KS
+    // slices of K, then the epilogue.
     constexpr int NOUT = SW ? NC / 2 : NC;
 #pragma unroll
-    for (int f = 0; f < MT; ++f) {
-        if (16 * f >= M) break;  // uniform over the workgroup
-        if (f) __syncthreads();  // the previous fragment's partial sums have been read
+    for (int q = 0; q < NC; ++q) part[2 + q][wave][lane] = acc[q];
+    part[0][wave][lane] = sx;
+    part[1][wave][lane] = sxx;
+    __syncthreads();
+    for (int j = wave; j < NOUT && nb0 + (SW ? 2 * j : j) < nblocks; j += KS) {
+        const int q0 = SW ? 2 * j : j;
+        const int64_t col = (nb0 + q0) * 16 + (lane & 15);
+        const int64_t n = min(col, N - 1), nu = min(col + 16, N - 1);
+        f32x4 tot[4];  // block q0, the moments, block q0 + 1 (SW)
 #pragma unroll
-        for (int q = 0; q < NC; ++q) part[2 + q][wave][lane] = acc[f][q];
-        part[0][wave][lane] = sx[f];
-        part[1][wave][lane] = sxx[f];
-        __syncthreads();
-        for (int j = wave; j < NOUT && nb0 + (SW ? 2 * j : j) < nblocks; j += KS) {
-            const int q0 = SW ? 2 * j : j;
-            const int64_t col = (nb0 + q0) * 16 + (lane & 15);
-            const int64_t n = min(col, N - 1), nu = min(col + 16, N - 1);
-            f32x4 tot[4];  // block q0, the moments, block q0 + 1 (SW)
-#pragma unroll
-            for (int w = 0; w < KS; ++w) {
-                const f32x4 v0 = part[2 + q0][w][lane], v1 = part[0][w][lane], v2 = part[1][w][lane];
-                tot[0] = w ? tot[0] + v0 : v0;
-                tot[1] = w ? tot[1] + v1 : v1;
-                tot[2] = w ? tot[2] + v2 : v2;
-                if constexpr (SW) tot[3] = w ? tot[3] + part[3 + q0][w][lane] : part[3 + q0][w][lane];
-            }
-            if constexpr (PLAIN) {
-                const float bn = bias ? (float)bias[n] : 0.f;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int r = 16 * f + 4 * (lane >> 4) + i;
-                    if (r < M && col < N) out[(int64_t)r * N + col] = (__bf16)(tot[0][i] + bn);
-                }
-                continue;
-            }
-            // Gram diagonal (r, r) sits in lane r + 16*(r>>2), element r&3.  This lane's
-            // rows are r = 4*(l>>4) + i of the fragment, so the source lane is 20*(l>>4) + i.
-            float diag[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) diag[i] = __shfl(tot[2][i], 20 * (lane >> 4) + i);
-            const float cn = c_col[n], bn = b_col[n];
-            const float cu = SW ? c_col[nu] : 0.f, bu = SW ? b_col[nu] : 0.f;
-            const int64_t o = SW ? (nb0 / 2 + j) * 16 + (lane & 15) : col;
+        for (int w = 0; w < KS; ++w) {
+            const f32x4 v0 = part[2 + q0][w][lane], v1 = part[0][w][lane], v2 = part[1][w][lane];
+            tot[0] = w ? tot[0] + v0 : v0;
+            tot[1] = w ? tot[1] + v1 : v1;
+            tot[2] = w ? tot[2] + v2 : v2;
+            if constexpr (SW) tot[3] = w ? tot[3] + part[3 + q0][w][lane] : part[3 + q0][w][lane];
+        }
+        if constexpr (PLAIN) {
+            const float bn = bias ? (float)bias[n] : 0.f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int r = 16 * f + 4 * (lane >> 4) + i;
-                float mean = rms ? 0.f : tot[1][i] / (float)K;
-                float rstd = rstd_from_moments(diag[i] / (float)K, mean, eps);
-                if (row_stats) {  // serial ablation (the moment products above are then unused)
-                    mean = row_stats[2 * min(r, M - 1)];
-                    rstd = row_stats[2 * min(r, M - 1) + 1];
-                }
-                if (stats_out && blockIdx.x == 0 && j == 0 && (lane & 15) == 0 && r < M) {
-                    stats_out[2 * r] = mean;  // the first column block's lanes export them, once per row
-                    stats_out[2 * r + 1] = rstd;
-                }
-                float v = __builtin_fmaf(rstd, __builtin_fmaf(-mean, cn, tot[0][i]), bn);
-                if constexpr (SW) v = silu(v) * __builtin_fmaf(rstd, __builtin_fmaf(-mean, cu, tot[3][i]), bu);
-                if (r < M && o < n_out) out[(int64_t)r * n_out + o] = (__bf16)v;
+                const int r = 4 * (lane >> 4) + i;
+                if (r < M && col < N) out[(int64_t)r * N + col] = (__bf16)(tot[0][i] + bn);
             }
+            continue;
+        }
+        // Gram diagonal (r, r) sits in lane r + 16*(r>>2), element r&3.  This lane's
+        // rows are r = 4*(l>>4) + i, so the source lane is 20*(l>>4) + i.
+        float diag[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) diag[i] = __shfl(tot[2][i], 20 * (lane >> 4) + i);
+        const float cn = c_col[n], bn = b_col[n];
+        const float cu = SW ? c_col[nu] : 0.f, bu = SW ? b_col[nu] : 0.f;
+        const int64_t o = SW ? (nb0 / 2 + j) * 16 + (lane & 15) : col;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 4 * (lane >> 4) + i;
+            float mean = rms ? 0.f : tot[1][i] / (float)K;
+            float rstd = rstd_from_moments(diag[i] / (float)K, mean, eps);
+            if (row_stats) {  // serial ablation (the moment products above are then unused)
+                mean = row_stats[2 * min(r, M - 1)];
+                rstd = row_stats[2 * min(r, M - 1) + 1];
+            }
+            if (stats_out && blockIdx.x == 0 && j == 0 && (lane & 15) == 0 && r < M) {
+                stats_out[2 * r] = mean;  // the first column block's lanes export them, once per row
+                stats_out[2 * r + 1] = rstd;
+            }
+            float v = __builtin_fmaf(rstd, __builtin_fmaf(-mean, cn, tot[0][i]), bn);
+            if constexpr (SW) v = silu(v) * __builtin_fmaf(rstd, __builtin_fmaf(-mean, cu, tot[3][i]), bu);
+            if (r < M && o < n_out) out[(int64_t)r * n_out + o] = (__bf16)v;
         }
     }
 }
@@ -1443,39 +1390,57 @@ static MainArgs packed_args(const void* A, const void* packed, int64_t M, int64_
 // for the partial sums).  Measured on the 8192 x 28672 up-projection (1792
 // blocks, nc = 7): 78.5-78.8 us for 1-16 tokens, against 81-91 us for the
 // 4- and 8-wave layouts with 1-4 blocks per workgroup.
-constexpr int64_t kDecodeMaxRows = 128;
-// Past 64 tokens the streaming kernel re-reads x once per workgroup and stops
-// beating the 128 x 128 tiles once those fill most of the chip: measured at
-// 65-128 tokens, 1.7-2x faster for the 4096 -> 12288 projection (96 tiles),
-// 1.15-1.4x slower for 8192 -> 28672 (224 tiles); the crossover sits near 160.
-static bool decode_rows(int64_t M, int64_t ncols) {
-    if (M <= 64) return true;
-    return M <= kDecodeMaxRows && ((M + 127) / 128) * ((ncols + 127) / 128) < 160;
-}
-template <bool PLAIN, int MT, int KS, int U, int NC, class F>
-static void decode_dispatch_nc(int64_t nc, F&& launch) {  // min(nc, NC) column blocks per workgroup
+constexpr int64_t kDecodeRows = 16;
+template <bool PLAIN, int NC, class F>
+static void decode_dispatch(int64_t nblocks, F&& launch) {  // ceil(nblocks / 256) column blocks, at most NC
     if constexpr (NC > 1)
-        if (nc < NC) return decode_dispatch_nc<PLAIN, MT, KS, U, NC - 1>(nc, launch);
-    launch(ln_decode_bf16_kernel<KS, NC, U, false, PLAIN, MT>, KS, NC);
+        if ((nblocks + 255) / 256 < NC) return decode_dispatch<PLAIN, NC - 1>(nblocks, launch);
+    launch(ln_decode_bf16_kernel<16, NC, 1, false, PLAIN>, 16, NC);
 }
-template <bool PLAIN, class F>
-static void decode_dispatch(int64_t M, int64_t nblocks, F&& launch) {
-    const int64_t nc = std::min<int64_t>(7, std::max<int64_t>(1, (nblocks + 255) / 256));
-    // 17-128 tokens: 2-8 row fragments per wave and 4 (8 at 6 fragments) waves
-    // splitting K; past 4 fragments at most 3 column blocks per workgroup (the
-    // accumulators of 8 fragments x 3 blocks take 96 registers per lane)
-    if (M <= 16)
-        decode_dispatch_nc<PLAIN, 1, 16, 1, 7>(nc, launch);
-    else if (M <= 32)
-        decode_dispatch_nc<PLAIN, 2, 4, 2, 7>(nc, launch);
-    else if (M <= 48)
-        decode_dispatch_nc<PLAIN, 3, 4, 2, 7>(nc, launch);
-    else if (M <= 64)
-        decode_dispatch_nc<PLAIN, 4, 4, 2, 7>(nc, launch);
-    else if (M <= 96)
-        decode_dispatch_nc<PLAIN, 6, 8, 1, 3>(nc, launch);
-    else
-        decode_dispatch_nc<PLAIN, 8, 4, 2, 3>(nc, launch);
+
+// The streamed few-row kernel against the tiles.  Up to 128 rows it always runs (4096 -> 12288
+// at 24 / 50 / 100 rows 21 / 24 / 32 us, where the decode layout with 2 - 8 row fragments per
+// wave took 24 / 38 / 55 us on the same card; 8192 -> 28672 at 60 / 100 rows 79 / 95 against
+// 125 / 144 us).  Past that it runs where its estimate is below the tiles' (us, same cards):
+// 200 rows 4096 -> 12288 43 / 63, 313 and 500 rows 4096 -> 6144 35 / 58 and 40 / 59, 300 rows
+// 768 -> 3072 9 / 17; at 1000 rows 4096 -> 12288 it would take 151 against 105.
+// Tiles, per 64 k: 128 x 128 in one round 0.83 us, 256 x 256 1.3 us (1.6 us with the chip full
+// and its clock down), the two-stage 128 x 128 loop 1.6 us alone and 1.9 us two to a CU.
+static double tiles_estimate_us(int64_t M, int64_t N, int64_t K, bool grouped) {
+    const double k64 = (double)K / 64.0;
+    if (use_mid_tiles(M, N, K)) return 5.0 + k64 * 0.83;
+    const int64_t tm = (M + 255) / 256;
+    if (use_big_tiles(M, N, K)) {
+        const TilePlan sq = plan_tiles(tm, (N + 255) / 256, grouped), na = plan_tiles(tm, (N + 191) / 192, grouped);
+        const double full = (sq.wgs >= 192 ? 1.6 : 1.3) * k64;
+        return 5.0 + full * std::min((double)sq.times, (double)na.times * kNarrowCost);
+    }
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);  // two fit a CU
+    return 5.0 + (tiles > 256 ? 1.9 : 1.6) * k64 * (double)((tiles + 511) / 512);
+}
+static bool use_skinny(int64_t M, int64_t N, int64_t K, int64_t nblocks, int dtype, bool gated, bool plain) {
+    if (dtype != 1 || M <= kDecodeRows || K >= (int64_t(1) << 22)) return false;
+    return M <= 128 || skinny_estimate_us(M, K, nblocks, gated) < 0.95 * tiles_estimate_us(M, N, K, !plain);
+}
+static hipError_t run_skinny(const MainArgs& a, int64_t n_out, bool gated, bool plain, hipStream_t s) {
+    SkinnyArgs k{};
+    k.x = a.A;
+    k.W = a.B;
+    k.bias = a.bias;
+    k.out = a.C;
+    k.M = a.M;
+    k.K = a.K;
+    k.N = a.N;
+    k.n_out = n_out;
+    k.kchunks = a.kchunks;
+    k.nblocks = a.nblocks;
+    k.c_col = a.c_col;
+    k.b_col = a.b_col;
+    k.eps = a.eps;
+    k.rms = a.rms;
+    k.row_stats = a.row_stats;
+    k.stats_out = a.stats_out;
+    return launch_skinny(k, gated, plain, s);
 }
 
 hipError_t launch_ln_linear_deferred(const void* x, const void* packed, int64_t M, int64_t K, int64_t N,
@@ -1486,16 +1451,17 @@ hipError_t launch_ln_linear_deferred(const void* x, const void* packed, int64_t 
     a.rms = rms;
     a.row_stats = row_stats;
     a.stats_out = stats_out;
-    if (dtype == 1 && decode_rows(M, N)) {
+    if (dtype == 1 && M <= kDecodeRows) {
         auto launch = [&](auto kern, int ks, int cols) {
             const int64_t wgs = (a.nblocks + cols - 1) / cols;
             kern<<<dim3((unsigned)wgs), ks * kWave, 0, s>>>((const __bf16*)x, (const char*)a.B, a.kchunks,
                                                             a.nblocks, a.c_col, a.b_col, (int)M, K, N, eps, rms,
                                                             N, a.row_stats, a.stats_out, (__bf16*)out, nullptr);
         };
-        decode_dispatch<false>(M, a.nblocks, launch);
+        decode_dispatch<false, 7>(a.nblocks, launch);
         return hipGetLastError();
     }
+    if (use_skinny(M, N, K, a.nblocks, dtype, false, false)) return run_skinny(a, N, false, false, s);
     if (dtype == 0) return run_main<float, 32, 64, 2, 2, BMode::kPacked, Epi::kLnDeferred, kF32Stages, kF32Chunks>(a, 1, s);
     if (use_mid_tiles(M, N, K)) return run_pipe<Epi::kLnDeferred, 128>(a, s);
     if (use_big_tiles(M, N, K)) return run_pipe<Epi::kLnDeferred>(a, s);
@@ -1527,34 +1493,20 @@ hipError_t launch_swiglu_deferred(const void* x, const void* packed, int64_t M, 
     a.eps = eps;
     a.rms = rms;
     a.n_out = N;
-    if (dtype == 1 && decode_rows(M, np)) {
+    if (dtype == 1 && M <= kDecodeRows) {
         auto launch = [&](auto kern, int ks, int cols) {
             const int64_t wgs = (a.nblocks + cols - 1) / cols;
             kern<<<dim3((unsigned)wgs), ks * kWave, 0, s>>>((const __bf16*)x, (const char*)a.B, a.kchunks, a.nblocks,
                                                            a.c_col, a.b_col, (int)M, K, np, eps, rms, N,
                                                            nullptr, nullptr, (__bf16*)out, nullptr);
         };
-        // up to 16 tokens: up to 7 gate/up block pairs per workgroup (about one
-        // workgroup per CU), 4 K-slices, 2-chunk groups -- on the 8192 x 2 x 28672
-        // weights 154.5 us (6.1 TB/s) for 1 token against 166.3 us with one pair per
-        // workgroup and 154.9 us with 8 K-slices; 33-64 tokens two pairs per workgroup
-        // (48 / 64 tokens: 220 / 276 us against 262 / 309 us with one; three pairs
-        // 258 / 307 us); 17-32 and 65-128 tokens one pair
-        if (M <= 16)
-            swiglu_dispatch_nc<14>(2 * std::min<int64_t>(7, std::max<int64_t>(1, (a.nblocks / 2 + 255) / 256)),
-                                   launch);
-        else if (M <= 32)
-            launch(ln_decode_bf16_kernel<4, 2, 2, true, false, 2>, 4, 2);
-        else if (M <= 48)
-            launch(ln_decode_bf16_kernel<4, 4, 2, true, false, 3>, 4, 4);
-        else if (M <= 64)
-            launch(ln_decode_bf16_kernel<4, 4, 2, true, false, 4>, 4, 4);
-        else if (M <= 96)
-            launch(ln_decode_bf16_kernel<4, 2, 2, true, false, 6>, 4, 2);
-        else
-            launch(ln_decode_bf16_kernel<4, 2, 2, true, false, 8>, 4, 2);
+        // up to 7 gate/up block pairs per workgroup (about one workgroup per CU), 4 K-slices,
+        // 2-chunk groups -- on the 8192 x 2 x 28672 weights 154.5 us (6.1 TB/s) for 1 token
+        // against 166.3 us with one pair per workgroup and 154.9 us with 8 K-slices
+        swiglu_dispatch_nc<14>(2 * std::min<int64_t>(7, std::max<int64_t>(1, (a.nblocks / 2 + 255) / 256)), launch);
         return hipGetLastError();
     }
+    if (use_skinny(M, np, K, a.nblocks, dtype, true, false)) return run_skinny(a, N, true, false, s);
     if (dtype == 0) return run_main<float, 32, 64, 2, 2, BMode::kPacked, Epi::kSwiGlu, kF32Stages, kF32Chunks>(a, 1, s);
     if (use_mid_tiles(M, np, K)) return run_pipe<Epi::kSwiGlu, 128>(a, s);
     if (use_big_tiles(M, np, K)) return run_pipe<Epi::kSwiGlu>(a, s);
@@ -1580,7 +1532,7 @@ hipError_t launch_gemm(const void* A, const void* B, const void* bias, int64_t b
     a.bias = bias;
     a.a_causal = a_causal;
     if (b_layout == 2) {
-        if (dtype == 1 && decode_rows(M, N)) {
+        if (dtype == 1 && M <= kDecodeRows) {
             // decode shapes: the streaming kernel of the deferred path without its moments,
             // in the same layouts (so the unfused comparison is like for like)
             auto launch = [&](auto kern, int ks, int cols) {
@@ -1590,9 +1542,10 @@ hipError_t launch_gemm(const void* A, const void* B, const void* bias, int64_t b
                                                                 N, nullptr, nullptr, (__bf16*)C,
                                                                 (const __bf16*)bias);
             };
-            decode_dispatch<true>(M, a.nblocks, launch);
+            decode_dispatch<true, 7>(a.nblocks, launch);
             return hipGetLastError();
         }
+        if (use_skinny(M, N, K, a.nblocks, dtype, false, true)) return run_skinny(a, N, false, true, s);
         if (dtype == 0) return run_main<float, 32, 64, 2, 2, BMode::kPacked, Epi::kGemm, kF32Stages, kF32Chunks>(a, 1, s);
         if (use_mid_tiles(M, N, K)) return run_pipe<Epi::kGemm, 128>(a, s);
         if (use_big_tiles(M, N, K)) return run_pipe<Epi::kGemm>(a, s);

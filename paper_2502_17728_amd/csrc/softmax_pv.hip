@@ -50,12 +50,6 @@ namespace dn {
 constexpr float kLog2e = 1.4426950408889634f;
 
 namespace sm {
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4)); }
 // vmcnt wait that also orders the compiler's memory operations: every memory
 // operation of the main loop is issued from inline assembly, so every wait on
 // them is written by hand.
@@ -63,11 +57,6 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt_asm() {
     static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ void block_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
 }
 // v_max3_f32 directly: fmaxf on values assembled from bit operations gets an
 // extra canonicalizing max per operand from the compiler.  Its operands are

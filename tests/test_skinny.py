@@ -1,0 +1,78 @@
+"""The streamed few-row kernel (17 rows and up, bf16) at the sizes where it can go wrong: every
+row-block height and its remainders, more than one row block, K that ends inside a 32- or
+64-k chunk or within the first stage, ragged column blocks; LayerNorm, RMSNorm, gated and
+plain.  Rows of guard values around the output must survive.
+
+Bounds: the row-normwise bound of the parity tests, and on the 2-norm of the whole error
+4e-3 (gated 6e-3): W' and the output round to bf16 once each, 2^-9 / sqrt(3) rms at most
+apiece (1.6e-3 together), the gated product has two such factors and K-long fp32 sums add
+far less.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2502_17728_amd import inputs as I
+from tests.parity import TOL, cuda, rowwise_rel_err
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(17, 8, 8), (32, 40, 24), (33, 72, 136), (48, 64, 4104), (49, 1000, 264), (64, 200, 1000), (65, 96, 72),
+          (96, 328, 520), (97, 136, 2056), (128, 2056, 40), (129, 1000, 1032), (200, 72, 4096), (257, 520, 776),
+          (300, 768, 3072), (815, 104, 328)]
+
+
+def _guarded(M, N):
+    buf = torch.full((M + 2, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    return buf, buf[1:M + 1]
+
+
+def _check(buf, ref, tol2):
+    torch.cuda.synchronize()
+    out = buf.cpu()
+    assert (out[0] == 7).all() and (out[-1] == 7).all()
+    got = out[1:-1]
+    assert rowwise_rel_err(got, ref) <= TOL[torch.bfloat16]
+    assert np.linalg.norm(oracle.to_f64(got) - ref) <= tol2 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("M,K,N", SHAPES)
+def test_linear(M, K, N):
+    from paper_2502_17728_amd import ops
+    for norm in ("layernorm", "rms"):
+        c = I.make_ln_case(M, K, N, "bf16", seed=M + K, norm=norm)
+        w = ops.ln_linear_prepare(cuda(c["W"]), cuda(c["gamma"]), cuda(c["beta"]))
+        buf, out = _guarded(M, N)
+        if norm == "rms":
+            ops.rms_linear_deferred(cuda(c["x"]), w, c["eps"], out=out)
+            ref = oracle.rms_linear(c["x"], c["gamma"], c["W"], None, c["eps"])
+        else:
+            ops.ln_linear_deferred(cuda(c["x"]), w, c["eps"], out=out)
+            ref = oracle.ln_linear(c["x"], c["gamma"], c["beta"], c["W"], None, c["eps"])
+        _check(buf, ref, 4e-3)
+
+
+@pytest.mark.parametrize("M,K,N", [(17, 40, 24), (40, 72, 264), (64, 1000, 3592), (80, 328, 2056), (128, 136, 1032),
+                                   (200, 64, 136)])
+def test_gated(M, K, N):
+    from paper_2502_17728_amd import ops
+    c = I.make_swiglu_case(M, K, N, "bf16", seed=M + K)
+    w = ops.swiglu_prepare(cuda(c["Wg"]), cuda(c["Wu"]), cuda(c["gamma"]))
+    buf, out = _guarded(M, N)
+    ops.rms_swiglu_deferred(cuda(c["x"]), w, c["eps"], out=out)
+    _check(buf, oracle.rms_swiglu(c["x"], c["gamma"], c["Wg"], c["Wu"], c["eps"]), 6e-3)
+
+
+@pytest.mark.parametrize("M,K,N", [(17, 40, 24), (50, 1000, 264), (128, 72, 1032), (300, 136, 520)])
+def test_plain(M, K, N):
+    # gemm on packed weights (gamma = 1), with a bias
+    from paper_2502_17728_amd import ops
+    c = I.make_ln_case(M, K, N, "bf16", seed=M)
+    one = torch.ones(K, dtype=torch.bfloat16)
+    w = ops.ln_linear_prepare(cuda(c["W"]), cuda(one))
+    bias = torch.linspace(-1, 1, N).to(torch.bfloat16)
+    buf, out = _guarded(M, N)
+    ops.gemm(cuda(c["x"]), w, cuda(bias), out=out.unsqueeze(0))
+    ref = oracle.to_f64(c["x"]) @ oracle.to_f64(c["W"]) + oracle.to_f64(bias)
+    _check(buf, ref, 4e-3)
