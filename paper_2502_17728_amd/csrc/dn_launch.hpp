@@ -43,8 +43,8 @@ hipError_t launch_ln_linear_deferred(const void* x, const void* packed, int64_t 
                                      int64_t N, int dtype, float eps, int rms, const float* row_stats,
                                      void* out, hipStream_t s, float* stats_out = nullptr);
 
-// Products of few rows (bf16, W' packed): row blocks of 32 .. 128 rows, both operands streamed
-// through LDS rings.  x below 2^31 bytes per row block (K < 2^22).  gated: N counts packed
+// Products on packed weights, row blocks of 16 .. 128 rows, both operands streamed through LDS
+// rings: bf16 of few rows, fp32 of any.  K < 2^22 (32-bit copy offsets; the prepare calls refuse more).  gated: N counts packed
 // columns and n_out the output features.  plain: no normalization, bias [N] (nullable).
 struct SkinnyArgs {
     const void* x;
@@ -59,7 +59,8 @@ struct SkinnyArgs {
     const float* row_stats;
     float* stats_out;
 };
-hipError_t launch_skinny(const SkinnyArgs& a, bool gated, bool plain, hipStream_t s);
+hipError_t launch_skinny(const SkinnyArgs& a, bool gated, bool plain, hipStream_t s);      // bf16
+hipError_t launch_skinny_f32(const SkinnyArgs& a, bool gated, bool plain, hipStream_t s);  // fp32
 double skinny_estimate_us(int64_t M, int64_t K, int64_t nblocks, bool gated);
 
 // y = (x - mean) rstd gamma + beta from per-row (mean, rstd); beta nullable.

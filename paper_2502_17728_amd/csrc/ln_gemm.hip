@@ -68,9 +68,9 @@ struct MainArgs {
 };
 
 // =============================================================================
-// General main loop: 128x128 (bf16) or 32x64 (fp32) tiles.  Used for problems
-// too small for the 256x256 kernel, for K not a multiple of 64, for fp32, for
-// batched products and for B in [K][N] layout.
+// General main loop: 128x128 (bf16) or 32x64 (fp32) tiles.  Used for packed bf16
+// products with K not a multiple of 64 that the few-row kernel does not take, for
+// batched products and for B in [K][N] or [N][K] layout.
 // NST = 2: two LDS stages, the copy of stage s+1 issued while stage s is read.
 // NST > 2 (chunk copies only, NST >= 3): a ring of NST stages whose copies run
 // NST-1 stages ahead, with each stage's fragments read while the previous
@@ -1227,9 +1227,8 @@ static hipError_t run_main(const MainArgs& a, int64_t batch, hipStream_t s) {
     main_loop_kernel<T, BM, BN, WM, WN, BMODE, EPI, NST, KBT><<<grid, WM * WN * kWave, 0, s>>>(a);
     return hipGetLastError();
 }
-// fp32 tiles (32 x 64, 4 waves): 4 chunks (64 k) per stage, a 4-stage ring of 24 KiB stages,
-// copies three stages ahead (LN -> Linear 128 x 768 x 3072: 15.3 us against 17.9 us with
-// 2-chunk stages in a 6-stage ring and 20.5 us with two 2-chunk stages)
+// fp32 tiles of the plain product with B as [N][K] (32 x 64, 4 waves): 4 chunks (64 k) per
+// stage, a 4-stage ring of 24 KiB stages, copies three stages ahead.
 constexpr int kF32Stages = 4, kF32Chunks = 4;
 
 // Mailbox of the shared row moments: 2 words per row, each (call number << 32) | fp32
@@ -1419,10 +1418,12 @@ static double tiles_estimate_us(int64_t M, int64_t N, int64_t K, bool grouped) {
     return 5.0 + (tiles > 256 ? 1.9 : 1.6) * k64 * (double)((tiles + 511) / 512);
 }
 static bool use_skinny(int64_t M, int64_t N, int64_t K, int64_t nblocks, int dtype, bool gated, bool plain) {
-    if (dtype != 1 || M <= kDecodeRows || K >= (int64_t(1) << 22)) return false;
+    if (K >= (int64_t(1) << 22)) return false;
+    if (dtype == 0) return true;
+    if (M <= kDecodeRows) return false;
     return M <= 128 || skinny_estimate_us(M, K, nblocks, gated) < 0.95 * tiles_estimate_us(M, N, K, !plain);
 }
-static hipError_t run_skinny(const MainArgs& a, int64_t n_out, bool gated, bool plain, hipStream_t s) {
+static hipError_t run_skinny(const MainArgs& a, int64_t n_out, int dtype, bool gated, bool plain, hipStream_t s) {
     SkinnyArgs k{};
     k.x = a.A;
     k.W = a.B;
@@ -1440,7 +1441,7 @@ static hipError_t run_skinny(const MainArgs& a, int64_t n_out, bool gated, bool 
     k.rms = a.rms;
     k.row_stats = a.row_stats;
     k.stats_out = a.stats_out;
-    return launch_skinny(k, gated, plain, s);
+    return dtype == 0 ? launch_skinny_f32(k, gated, plain, s) : launch_skinny(k, gated, plain, s);
 }
 
 hipError_t launch_ln_linear_deferred(const void* x, const void* packed, int64_t M, int64_t K, int64_t N,
@@ -1461,8 +1462,8 @@ hipError_t launch_ln_linear_deferred(const void* x, const void* packed, int64_t 
         decode_dispatch<false, 7>(a.nblocks, launch);
         return hipGetLastError();
     }
-    if (use_skinny(M, N, K, a.nblocks, dtype, false, false)) return run_skinny(a, N, false, false, s);
-    if (dtype == 0) return run_main<float, 32, 64, 2, 2, BMode::kPacked, Epi::kLnDeferred, kF32Stages, kF32Chunks>(a, 1, s);
+    if (use_skinny(M, N, K, a.nblocks, dtype, false, false)) return run_skinny(a, N, dtype, false, false, s);
+    if (dtype == 0) return hipErrorInvalidValue;  // K >= 2^22, which the prepare calls refuse
     if (use_mid_tiles(M, N, K)) return run_pipe<Epi::kLnDeferred, 128>(a, s);
     if (use_big_tiles(M, N, K)) return run_pipe<Epi::kLnDeferred>(a, s);
     return run_main<__bf16, 128, 128, 2, 2, BMode::kPacked, Epi::kLnDeferred>(a, 1, s);
@@ -1506,8 +1507,8 @@ hipError_t launch_swiglu_deferred(const void* x, const void* packed, int64_t M, 
         swiglu_dispatch_nc<14>(2 * std::min<int64_t>(7, std::max<int64_t>(1, (a.nblocks / 2 + 255) / 256)), launch);
         return hipGetLastError();
     }
-    if (use_skinny(M, np, K, a.nblocks, dtype, true, false)) return run_skinny(a, N, true, false, s);
-    if (dtype == 0) return run_main<float, 32, 64, 2, 2, BMode::kPacked, Epi::kSwiGlu, kF32Stages, kF32Chunks>(a, 1, s);
+    if (use_skinny(M, np, K, a.nblocks, dtype, true, false)) return run_skinny(a, N, dtype, true, false, s);
+    if (dtype == 0) return hipErrorInvalidValue;  // K >= 2^22, which the prepare calls refuse
     if (use_mid_tiles(M, np, K)) return run_pipe<Epi::kSwiGlu, 128>(a, s);
     if (use_big_tiles(M, np, K)) return run_pipe<Epi::kSwiGlu>(a, s);
     return run_main<__bf16, 128, 128, 2, 2, BMode::kPacked, Epi::kSwiGlu>(a, 1, s);
@@ -1545,8 +1546,8 @@ hipError_t launch_gemm(const void* A, const void* B, const void* bias, int64_t b
             decode_dispatch<true, 7>(a.nblocks, launch);
             return hipGetLastError();
         }
-        if (use_skinny(M, N, K, a.nblocks, dtype, false, true)) return run_skinny(a, N, false, true, s);
-        if (dtype == 0) return run_main<float, 32, 64, 2, 2, BMode::kPacked, Epi::kGemm, kF32Stages, kF32Chunks>(a, 1, s);
+        if (use_skinny(M, N, K, a.nblocks, dtype, false, true)) return run_skinny(a, N, dtype, false, true, s);
+        if (dtype == 0) return hipErrorInvalidValue;  // K >= 2^22, which the prepare calls refuse
         if (use_mid_tiles(M, N, K)) return run_pipe<Epi::kGemm, 128>(a, s);
         if (use_big_tiles(M, N, K)) return run_pipe<Epi::kGemm>(a, s);
         return run_main<__bf16, 128, 128, 2, 2, BMode::kPacked, Epi::kGemm>(a, 1, s);

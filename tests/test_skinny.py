@@ -76,3 +76,27 @@ def test_plain(M, K, N):
     ops.gemm(cuda(c["x"]), w, cuda(bias), out=out.unsqueeze(0))
     ref = oracle.to_f64(c["x"]) @ oracle.to_f64(c["W"]) + oracle.to_f64(bias)
     _check(buf, ref, 4e-3)
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 8, 8), (3, 40, 24), (16, 1000, 264), (17, 24, 136), (33, 72, 4104),
+                                   (64, 328, 520), (65, 136, 72), (128, 768, 1032), (129, 200, 40), (300, 104, 776),
+                                   (1000, 16, 328)])
+def test_fp32(M, K, N):
+    # every fp32 product on packed weights: LayerNorm, RMSNorm with its exported statistics, gated, plain
+    from paper_2502_17728_amd import ops
+    tol = TOL[torch.float32]
+    c = I.make_ln_case(M, K, N, "f32", seed=M + K)
+    x, W = cuda(c["x"]), cuda(c["W"])
+    w = ops.ln_linear_prepare(W, cuda(c["gamma"]), cuda(c["beta"]))
+    out = ops.ln_linear_deferred(x, w, c["eps"])
+    assert rowwise_rel_err(out.cpu(), oracle.ln_linear(c["x"], c["gamma"], c["beta"], c["W"], None, c["eps"])) <= tol
+    w = ops.ln_linear_prepare(W, cuda(c["gamma"]))
+    out, y, stats = ops.linear_deferred_post(x, w, cuda(c["gamma"]), eps=c["eps"], rms=True)
+    assert rowwise_rel_err(out.cpu(), oracle.rms_linear(c["x"], c["gamma"], c["W"], None, c["eps"])) <= tol
+    assert rowwise_rel_err(y.cpu(), oracle.rmsnorm(c["x"], c["gamma"], c["eps"])) <= tol
+    out = ops.gemm(x, ops.ln_linear_prepare(W, torch.ones(K, device="cuda")))
+    assert rowwise_rel_err(out.cpu(), oracle.to_f64(c["x"]) @ oracle.to_f64(c["W"])) <= tol
+    g = I.make_swiglu_case(M, K, N, "f32", seed=M)
+    w = ops.swiglu_prepare(cuda(g["Wg"]), cuda(g["Wu"]), cuda(g["gamma"]))
+    out = ops.rms_swiglu_deferred(cuda(g["x"]), w, g["eps"])
+    assert rowwise_rel_err(out.cpu(), oracle.rms_swiglu(g["x"], g["gamma"], g["Wg"], g["Wu"], g["eps"])) <= tol
