@@ -295,9 +295,10 @@ DN_API dn_status attention_gqa_deferred(const void* Q, const void* K, const void
 /*
  * Decode-shaped attention: Lq <= 16 query rows per head against all Lk keys
  * (the key/value cache holds exactly the visible keys, so no mask).  The keys
- * are cut into ranges, one workgroup each, that leave their un-normalized
- * partial sums (acc, l and the reference max m, fp32) in `workspace`; one
- * merge kernel then combines them, m = max m_g, out = sum 2^(m_g - m) acc_g /
+ * of all heads are dealt evenly to one resident round of workgroups; where a
+ * head's keys went to several, each leaves its un-normalized partial sums
+ * (acc, l and the reference max m, fp32) in `workspace`, and one merge kernel
+ * combines them, m = max m_g, out = sum 2^(m_g - m) acc_g /
  * sum 2^(m_g - m) l_g -- the deferred division of Eq. (8) once more, across
  * key ranges.  workspace: caller-owned device memory of
  * attention_decode_workspace_bytes(BH, Lq, Lk, d) bytes, 16-byte aligned, not
@@ -307,9 +308,12 @@ DN_API dn_status attention_gqa_deferred(const void* Q, const void* K, const void
  * sharing each key/value head, the g heads consecutive): pass Q and out as
  * [BH][g * Lq][d] -- the same memory as [BH * g][Lq][d] -- with Lq := g * Lq
  * (<= 16), so each key/value tile read from HBM serves all g heads at once.
- * With enough heads to fill the chip the
- * keys are not split and one pass writes out directly (the workspace is then
- * not touched).  attention_decode_workspace_bytes
+ * Where every workgroup has whole heads one pass writes out directly (the
+ * workspace is then not touched).  A workspace smaller than
+ * attention_decode_workspace_bytes asks for is taken if it holds the partials
+ * of every head cut into equally many ranges, one workgroup each (BH * n * Lq
+ * * (d + 4) floats, n = about 256 / BH at d = 128, 512 / BH at d = 64); the
+ * keys are then cut that way.  attention_decode_workspace_bytes
  * returns 0 for an invalid request.
  */
 DN_API size_t attention_decode_workspace_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d);

@@ -311,7 +311,9 @@ DN_API dn_status attention_decode_deferred(const void* Q, const void* K, const v
     if (!bytes_of(BH, Lq, d * 2, &qb) || !bytes_of(BH, Lk, d * 2, &kb)) return DN_ERR_INVALID_ARG;
     if (dtype != DN_BF16 || (d != 64 && d != 128) || Lq > 16) return DN_ERR_UNSUPPORTED;
     if (Lk * d * 2 >= (int64_t(1) << 31)) return DN_ERR_UNSUPPORTED;
-    const size_t need = attention_decode_workspace_bytes(BH, Lq, Lk, d);
+    // the least a call can work with, and what attention_decode_workspace_bytes asks for
+    const size_t need = dn::attention_decode_least_bytes(BH, Lq, Lk, d);
+    const size_t full = dn::attention_decode_workspace_bytes(BH, Lq, Lk, d);
     if (need == 0 || workspace_bytes < need) return DN_ERR_INVALID_ARG;
     if (!aligned(Q, 16) || !aligned(K, 16) || !aligned(V, 16) || !aligned(out, 16) || !aligned(workspace, 16))
         return DN_ERR_MISALIGNED;
@@ -319,8 +321,13 @@ DN_API dn_status attention_decode_deferred(const void* Q, const void* K, const v
         overlaps(workspace, need, Q, qb) || overlaps(workspace, need, K, kb) || overlaps(workspace, need, V, kb) ||
         overlaps(workspace, need, out, qb))
         return DN_ERR_INVALID_ARG;
-    if (BH * 16 > kMaxGridX) return DN_ERR_UNSUPPORTED;  // grids: BH + 1280 splits, BH * Lq / 4 merges
-    return from_hip(dn::launch_attention_decode(Q, K, V, BH, Lq, Lk, d, scale, workspace, out, stream));
+    if (BH * 16 > kMaxGridX) return DN_ERR_UNSUPPORTED;  // grid: at most BH + 512 workgroups
+    // no more than the least is used where the rest is missing or belongs to another argument
+    const bool whole = workspace_bytes >= full && !overlaps(workspace, full, Q, qb) &&
+                       !overlaps(workspace, full, K, kb) && !overlaps(workspace, full, V, kb) &&
+                       !overlaps(workspace, full, out, qb);
+    return from_hip(dn::launch_attention_decode(Q, K, V, BH, Lq, Lk, d, scale, workspace, whole ? full : need, out,
+                                                stream));
 }
 
 DN_API dn_status attention_decode_deferred_noalloc(const void* Q, const void* K, const void* V, int64_t BH,

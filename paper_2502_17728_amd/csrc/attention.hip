@@ -33,12 +33,7 @@
 // (55 % at 2.0 GHz before the two halves of a workgroup ran out of phase), 473 us against
 // 521 us in one run; 4096 keys without a mask 221 us against 239 us.
 //
-// Decode (a few new queries against a long key/value cache).  One workgroup
-// per head would leave most CUs idle, so the keys of each head are cut into
-// ranges, one single-wave workgroup each, sized so that the grid is one
-// resident round; every range leaves (acc, l, m) in fp32 and a merge kernel
-// combines them with weights 2^(m_g - m) -- the deferred division of Eq. (8)
-// postponed once more, past the reduction over key ranges.
+// Decode (a few new queries against a long key/value cache): attention_kernel below.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -83,289 +78,6 @@ __device__ __forceinline__ uint2 lds_tr16(const char* p) {
     return __builtin_bit_cast(uint2, r);
 }
 }  // namespace fa
-
-// STREAM: every key/value row is read by one workgroup only (decode), so the copies
-// carry the non-temporal hint; prefill workgroups share them through L2.
-template <int D, int NW, int QW, int NS, int BKV, bool STREAM = false>
-__global__ __launch_bounds__(NW * 64) void attention_kernel(const __bf16* __restrict__ Q,
-                                                            const __bf16* __restrict__ K,
-                                                            const __bf16* __restrict__ V, int64_t Lq,
-                                                            int64_t Lk, int causal, float sl2, int nqb,
-                                                            int nsplit, int64_t kchunk, float* __restrict__ part,
-                                                            __bf16* __restrict__ out, int group) {
-    using namespace fa;
-    constexpr int BQ = NW * QW * 16;   // queries per workgroup
-    constexpr int NKB = BKV / 16;      // 16-key S^T blocks per step
-    constexpr int NKC = BKV / 32;      // 32-key chunks of the P.V product per step
-    constexpr int ROW = D * 2;         // bytes per K or V row
-    constexpr int TILE = BKV * ROW;    // one K (or V) tile
-    constexpr int SLOT = 2 * TILE;     // ring slot: K tile, then V tile
-    constexpr int T_INS = TILE / kChunkBytes / NW;  // copies per wave per tile
-    constexpr int KV_INS = 2 * T_INS;
-    constexpr int PPR = ROW / 16;      // 16-byte pieces per row
-    constexpr int RPI = kChunkBytes / ROW;  // rows per copy instruction
-    constexpr int DB = D / 16, DC = D / 32;
-    static_assert(TILE % (kChunkBytes * NW) == 0, "tiles split evenly over the waves");
-    static_assert(NS >= 2 && (NS - 2) * KV_INS < 64, "ring depth: the copies in flight fit vmcnt");
-
-    __shared__ __attribute__((aligned(1024))) char smem[NS * SLOT];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // logical id: XCD-contiguous; each XCD walks whole heads, longest query blocks first.
-    // Split mode (part != null): the keys are cut into nsplit ranges of kchunk, one per
-    // workgroup, each leaving its un-normalized partial sums for the merge kernel.
-    const int t0 = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int sp = t0 % nsplit, t = t0 / nsplit;
-    const int h = t / nqb;
-    const int qb = causal ? (nqb - 1 - t % nqb) : (t % nqb);
-    const int64_t q0 = (int64_t)qb * BQ;
-    const int64_t kv_end = causal ? min(Lk, q0 + BQ) : Lk;
-    const int64_t k_lo = (int64_t)sp * kchunk;                  // this workgroup's keys: [k_lo, k_hi)
-    const int64_t k_hi = min(kv_end, k_lo + kchunk);
-    const int nsteps = (int)((k_hi - k_lo + BKV - 1) / BKV);
-
-    const __bf16* Qh = Q + (int64_t)h * Lq * D;
-    // grouped-query attention: query head h reads key/value head h / group
-    const __bf16* Kh = K + (int64_t)(h / group) * Lk * D;
-    const __bf16* Vh = V + (int64_t)(h / group) * Lk * D;
-    __bf16* Oh = out + (int64_t)h * Lq * D;
-
-    const int64_t qw0 = q0 + wave * QW * 16;  // first query of this wave
-    const int G = lane >> 4, i = lane & 15;
-    int64_t qrow[QW];
-#pragma unroll
-    for (int f = 0; f < QW; ++f) qrow[f] = qw0 + f * 16 + i;
-
-    // Q^T fragments (B operand of S^T): lane (i, G) holds query 16f + i, d 32c + 8G .. +8
-    u32x4 qf[QW][DC];
-#pragma unroll
-    for (int f = 0; f < QW; ++f) {
-        const int64_t qr = qrow[f] < Lq ? qrow[f] : Lq - 1;
-#pragma unroll
-        for (int c = 0; c < DC; ++c) qf[f][c] = ld16(Qh + qr * D + 32 * c + 8 * G);
-    }
-    // Q is in registers before the key loop: each fragment is an operand of an empty
-    // statement here, so the compiler places its waits for these loads before the
-    // loop.  Left to find the first use inside it, it kept waits there on every
-    // step, and at run time those also drained the copies issued for the next step.
-#pragma unroll
-    for (int f = 0; f < QW; ++f)
-#pragma unroll
-        for (int c = 0; c < DC; ++c) asm volatile("" : "+v"(qf[f][c]));
-    wait_vmcnt_asm<0>();  // before the hand-counted copies below start
-
-    // ---- K/V ring.  Copy instruction j of a wave covers tile rows
-    // RPI * (wave + j * NW) .. + RPI; lane l fetches piece (l % PPR) ^ swz(row),
-    // so logical piece p of a row lands in slot p ^ swz(row).  Keys past Lk
-    // clamp onto the last row (their scores are masked); byte offsets from the
-    // head's base fit 32 bits (Lk * d * 2 < 2^32).
-    uint32_t c_row[T_INS], k_p16[T_INS], v_p16[T_INS];
-#pragma unroll
-    for (int j = 0; j < T_INS; ++j) {
-        const int r = (wave + j * NW) * RPI + lane / PPR;
-        c_row[j] = (uint32_t)r;
-        k_p16[j] = (uint32_t)(((lane % PPR) ^ k_swz<D>(r)) * 16);
-        v_p16[j] = (uint32_t)(((lane % PPR) ^ v_swz<D>(r)) * 16);
-    }
-    const uint64_t k_base = uniform_u64(Kh), v_base = uniform_u64(Vh);
-    const uint32_t last = (uint32_t)(Lk - 1);
-    const uint32_t smem_addr = lds_addr32(smem);
-    auto issue_kv = [&](int step) {
-        const uint32_t base = smem_addr + (uint32_t)((step % NS) * SLOT);
-        const uint32_t k0 = (uint32_t)k_lo + (uint32_t)step * BKV;
-#pragma unroll
-        for (int j = 0; j < T_INS; ++j) {
-            const uint32_t key = k0 + c_row[j] < last ? k0 + c_row[j] : last;  // a select, no branch
-            const uint32_t dst = base + (uint32_t)((wave + j * NW) * kChunkBytes);
-            if constexpr (STREAM) {
-                g2lds16_stream_sb(k_base, key * (uint32_t)ROW + k_p16[j], dst);
-                g2lds16_stream_sb(v_base, key * (uint32_t)ROW + v_p16[j], dst + TILE);
-            } else {
-                g2lds16_async_sb(k_base, key * (uint32_t)ROW + k_p16[j], dst);
-                g2lds16_async_sb(v_base, key * (uint32_t)ROW + v_p16[j], dst + TILE);
-            }
-        }
-    };
-
-    // Lane-constant LDS offsets.  K: row 16 kb + i, logical piece 4c + G (the
-    // swizzle depends on the row only through i).  V^T: two transposing reads
-    // per 16-wide d block, the first covering keys 4G .. 4G+3 of the chunk, the
-    // second keys 16+4G .. 16+4G+3 (within a 16-lane group, lane j, slot t gets
-    // element j & 3 of the 8 bytes lane 4t + (j >> 2) reads, so lane (i, G)
-    // reads row 4G + (i >> 2), d 4 (i & 3) .. +3 of the block).
-    int k_rd[DC];
-#pragma unroll
-    for (int c = 0; c < DC; ++c) k_rd[c] = i * ROW + (((4 * c + G) ^ k_swz<D>(i)) << 4);
-    const int vr = 4 * G + (i >> 2);
-    const int vsw2 = v_swz<D>(vr) >> 1;  // swizzle of the 32-byte d block
-    int v_off[DB];
-#pragma unroll
-    for (int b = 0; b < DB; ++b) v_off[b] = vr * ROW + (i & 3) * 8 + 32 * (b ^ vsw2);
-
-    f32x4 acc[QW][DB], accl[QW];
-#pragma unroll
-    for (int f = 0; f < QW; ++f) {
-#pragma unroll
-        for (int b = 0; b < DB; ++b) acc[f][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        accl[f] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
-
-    // Reference maximum per query in scaled log2 units, raised only when a step
-    // exceeds it by more than 8 (numerators stay below 256; the rescale of the
-    // partial sums, an exact identity, is rare).
-    float mref[QW];
-#pragma unroll
-    for (int f = 0; f < QW; ++f) mref[f] = -__builtin_inff();
-
-    const int qw0i = (int)qw0, kv_endi = (int)k_hi;  // positions fit 32 bits (checked by the host)
-    const int qlast = qw0i + QW * 16 - 1;              // this wave's last query
-
-    // scores S^T of one step: 4 blocks of 16 keys per query fragment
-    auto scores = [&](int step, f32x4(&st)[QW][NKB]) {
-        const char* kb = smem + (step % NS) * SLOT;
-#pragma unroll
-        for (int f = 0; f < QW; ++f)
-#pragma unroll
-            for (int b4 = 0; b4 < NKB; ++b4) st[f][b4] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int b4 = 0; b4 < NKB; ++b4)
-#pragma unroll
-            for (int c = 0; c < DC; ++c) {
-                const u32x4 kf = lds_ld16(lds_ptr((char*)kb + b4 * 16 * ROW + k_rd[c]));
-#pragma unroll
-                for (int f = 0; f < QW; ++f) st[f][b4] = mfma_chunk<__bf16>(kf, qf[f][c], st[f][b4]);
-            }
-    };
-    // numerators of one step (keys past the diagonal or past Lk masked first),
-    // with the reference max raised where needed; returns whether any lane raised it
-    auto numerators = [&](int step, f32x4(&st)[QW][NKB], u32x4(&pf)[QW][NKC], float(&alpha)[QW]) {
-        const int k0 = (int)k_lo + step * BKV;
-        if ((causal && k0 + BKV - 1 > qw0i) || k0 + BKV > kv_endi) {
-#pragma unroll
-            for (int f = 0; f < QW; ++f) {
-                const int lim = causal ? min((int)qrow[f], kv_endi - 1) : kv_endi - 1;
-#pragma unroll
-                for (int b4 = 0; b4 < NKB; ++b4) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (k0 + 16 * b4 + 4 * G + e > lim) st[f][b4][e] = -__builtin_inff();
-                    // one block's compare masks at a time: issued all at once they
-                    // took 64 SGPRs and pushed loop-long scalars into VGPR lanes
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        }
-        bool raised = false;
-#pragma unroll
-        for (int f = 0; f < QW; ++f) {
-            float tmax = st[f][0][0];
-#pragma unroll
-            for (int b4 = 0; b4 < NKB; ++b4)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) tmax = __builtin_fmaxf(tmax, st[f][b4][e]);
-            const float tmax2 = max_lane_groups(tmax) * sl2;
-            const bool raise = tmax2 > mref[f] + 8.0f;
-            const float mnew = raise ? tmax2 : mref[f];
-            alpha[f] = __builtin_amdgcn_exp2f(raise ? mref[f] - mnew : 0.f);
-            mref[f] = mnew;
-            raised |= raise;
-            const float nb = mnew == -__builtin_inff() ? 0.f : -mnew;
-            float p[NKB][4];
-#pragma unroll
-            for (int b4 = 0; b4 < NKB; ++b4)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) p[b4][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[f][b4][e], sl2, nb));
-#pragma unroll
-            for (int kc = 0; kc < NKC; ++kc)
-                pf[f][kc] = u32x4{pack_bf16(p[2 * kc][0], p[2 * kc][1]), pack_bf16(p[2 * kc][2], p[2 * kc][3]),
-                                  pack_bf16(p[2 * kc + 1][0], p[2 * kc + 1][1]),
-                                  pack_bf16(p[2 * kc + 1][2], p[2 * kc + 1][3])};
-        }
-        return raised;
-    };
-    // out^T += V^T . P~^T, keys of chunk kc in the order of the numerators
-    auto products = [&](int step, const u32x4(&pf)[QW][NKC]) {
-        const char* vb = smem + (step % NS) * SLOT + TILE;
-#pragma unroll
-        for (int kc = 0; kc < NKC; ++kc) {
-            u32x4 vf[DB];
-#pragma unroll
-            for (int b = 0; b < DB; ++b) {
-                const uint2 lo = lds_tr16(vb + v_off[b] + (kc * 32) * ROW);
-                const uint2 hi = lds_tr16(vb + v_off[b] + (kc * 32 + 16) * ROW);
-                vf[b] = u32x4{lo.x, lo.y, hi.x, hi.y};
-            }
-#pragma unroll
-            for (int b = 0; b < DB; ++b)
-#pragma unroll
-                for (int f = 0; f < QW; ++f) acc[f][b] = mfma_chunk<__bf16>(vf[b], pf[f][kc], acc[f][b]);
-#pragma unroll
-            for (int f = 0; f < QW; ++f) accl[f] = mfma_chunk<__bf16>(ones, pf[f][kc], accl[f]);
-        }
-    };
-    auto rescale = [&](bool raised, const float(&alpha)[QW]) {
-        if (__any(raised)) {
-#pragma unroll
-            for (int f = 0; f < QW; ++f) {
-#pragma unroll
-                for (int b = 0; b < DB; ++b) acc[f][b] *= alpha[f];
-                accl[f] *= alpha[f];
-            }
-        }
-    };
-    auto active = [&](int step) { return step < nsteps && !(causal && (int)k_lo + step * BKV > qlast); };
-
-    for (int s = 0; s < NS - 1; ++s) issue_kv(s);
-    for (int s = 0; s < nsteps; ++s) {
-        wait_vmcnt_asm<(NS - 2) * KV_INS>();  // this wave's copies of step s have landed
-        wait_lgkm0();                         // its LDS reads of step s-1 are done
-        block_barrier();                      // ... and every wave's
-        issue_kv(s + NS - 1);                 // into the slot step s-1 vacated
-        if (!active(s)) continue;             // wholly above this wave's queries
-        f32x4 st[QW][NKB];
-        scores(s, st);
-        u32x4 pf[QW][NKC];
-        float alpha[QW];
-        const bool raised = numerators(s, st, pf, alpha);
-        rescale(raised, alpha);
-        products(s, pf);
-    }
-    wait_vmcnt_asm<0>();  // no copy into LDS may outlive the workgroup
-
-    if (part) {
-        // split mode: the partial (acc[d], l, m, 2 pad) of each query row, fp32, for the merge
-#pragma unroll
-        for (int f = 0; f < QW; ++f) {
-            if (qrow[f] >= Lq) continue;
-            float* pr = part + (((int64_t)h * Lq + qrow[f]) * nsplit + sp) * (D + 4);  // 16-byte rows
-#pragma unroll
-            for (int b = 0; b < DB; ++b)
-                *reinterpret_cast<f32x4*>(pr + b * 16 + 4 * G) = acc[f][b];
-            if (G == 0) {
-                pr[D] = accl[f][0];
-                pr[D + 1] = mref[f];
-            }
-        }
-        return;
-    }
-
-    // ---- epilogue: the single deferred division, one rounding to bf16
-#pragma unroll
-    for (int f = 0; f < QW; ++f) {
-        if (qrow[f] >= Lq) continue;
-        const float inv = 1.0f / accl[f][0];
-        __bf16* orow = Oh + qrow[f] * D + 4 * G;
-#pragma unroll
-        for (int b = 0; b < DB; ++b) {
-            uint2 v;
-            v.x = pack_bf16(acc[f][b][0] * inv, acc[f][b][1] * inv);
-            v.y = pack_bf16(acc[f][b][2] * inv, acc[f][b][3] * inv);
-            *reinterpret_cast<uint2*>(orow + b * 16) = v;
-        }
-    }
-}
 
 // Prefill.  NQW x QW x 16 queries per workgroup; KSP groups of NQW waves walk KSP
 // contiguous runs of the key steps, each through its own K and V rings (two slots each),
@@ -498,7 +210,11 @@ __global__ __launch_bounds__(NQW* KSP * 64) void attention_prefill_kernel(
 #pragma unroll
         for (int c = 0; c < DC; ++c) asm volatile("" : "+v"(qf[f][c]));
 
-    // Lane-constant LDS offsets, as in attention_kernel.
+    // Lane-constant LDS offsets.  K: row 16 kb + i, logical piece 4c + G (the swizzle depends on
+    // the row only through i).  V^T: two transposing reads per 16-wide d block, the first
+    // covering keys 4G .. 4G+3 of the chunk, the second keys 16+4G .. 16+4G+3 (within a 16-lane
+    // group, lane j, slot t gets element j & 3 of the 8 bytes lane 4t + (j >> 2) reads, so lane
+    // (i, G) reads row 4G + (i >> 2), d 4 (i & 3) .. +3 of the block).
     int k_rd[DC];
 #pragma unroll
     for (int c = 0; c < DC; ++c) k_rd[c] = i * ROW + (((4 * c + G) ^ k_swz<D>(i)) << 4);
@@ -819,97 +535,358 @@ static hipError_t run_attention(const void* Q, const void* K, const void* V, int
     return hipGetLastError();
 }
 
-// Merge of the split partials (the log-sum-exp combination of Eq. (8) over key
-// ranges): m = max_g m_g, out = sum_g 2^(m_g - m) acc_g / sum_g 2^(m_g - m) l_g,
-// one wave per query row.
+// Decode: up to 16 query rows per head against all keys.  The keys of all heads, in units of
+// 128, are dealt evenly and in order to the workgroups of one resident round, so a workgroup
+// takes a run of units that may end one head and begin the next; whatever the head count and
+// cache length, no workgroup has more than one unit more than another.
+//
+// The four waves of a workgroup take 32 keys of each unit and stream them through K/V rings of
+// their own (two slots, no barrier; four waves keep up to 128 KiB in flight, one wave's counter
+// 63 KiB).  At the end of a head's run the waves' (acc, l, m) meet in LDS.  A head whose keys
+// one workgroup read whole is divided and written; otherwise the workgroup leaves its partial
+// sums in the workspace and a merge kernel combines the head's partials in key order -- Eq. (8)
+// over key ranges, m = max_g m_g, out = sum_g 2^(m_g - m) acc_g / sum_g 2^(m_g - m) l_g.  (The
+// last workgroup of a head to arrive combining them instead, with no second launch, measured the
+// same or slower: its waits for device-scope stores and loads cost what the launch does, and up
+// to 33 against 18 us where 32 workgroups share a head.)
+//
+// Bound by HBM.  Against one single-wave workgroup per equal range of each head (graph replays,
+// us): 177 heads x 11814 keys, d = 128 170 / 212 (that left a second round of 98 workgroups),
+// 300 x 1000 31 / 42, 17 x 1992 11.6 / 22.6, 64 x 5001 32 / 34, 37 x 7242, d = 64 19.6 / 23.9;
+// 256 x 8192, where every workgroup has one whole head, 156 / 154 (6.9 TB/s).
+struct DecodeArgs {
+    int64_t BH;
+    int Lq, Lk;
+    int units;       // per head, of 128 keys
+    int per;         // units per workgroup
+    int nsplit;      // > 0: every head in nsplit runs of `per` units, one workgroup each (a
+                     // workspace of the size that layout needs); 0: runs across heads
+    float sl2;
+
+    // The head's partials lie in a row from slot first_slot on: h + wg where a head spans several
+    // workgroups, 2 wg + .. where a workgroup spans heads (then a split head has two parts).
+    __device__ int first_wg(int h) const { return nsplit ? 0 : (int)((int64_t)h * units / per); }
+    __device__ int64_t first_slot(int h, int f) const {
+        return nsplit ? (int64_t)h * nsplit : per >= units ? 2 * (int64_t)f : (int64_t)h + f;
+    }
+    __device__ int parts(int h, int f) const {
+        return nsplit ? nsplit : (int)((((int64_t)h + 1) * units - 1) / per) - f + 1;
+    }
+};
 template <int D>
-__global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ part, int nsplit,
-                                                              int64_t rows, __bf16* __restrict__ out) {
-    constexpr int PER = D / 64;
+__global__ __launch_bounds__(256) void attention_kernel(const __bf16* __restrict__ Q,
+                                                               const __bf16* __restrict__ K,
+                                                               const __bf16* __restrict__ V, DecodeArgs p,
+                                                               float* __restrict__ part, __bf16* __restrict__ out) {
+    using namespace fa;
+    constexpr int ROW = D * 2, TILE = 32 * ROW, SLOT = 2 * TILE;  // 32 keys of K, then V
+    constexpr int INS = TILE / kChunkBytes;                       // copies per tile
+    constexpr int PPR = ROW / 16, RPI = kChunkBytes / ROW;
+    constexpr int DB = D / 16, DC = D / 32;
+    constexpr int PR = D + 4;  // floats per partial row: acc[d], l, m and 2 pad floats
+    __shared__ __attribute__((aligned(1024))) char smem[4 * 2 * SLOT];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int G = lane >> 4, i = lane & 15;
+    const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int64_t total = p.BH * p.units;
+    int64_t pos = p.nsplit ? (int64_t)(wg / p.nsplit) * p.units + (int64_t)(wg % p.nsplit) * p.per : (int64_t)wg * p.per;
+    const int64_t end = p.nsplit ? min((int64_t)(wg / p.nsplit + 1) * p.units, pos + p.per) : min(total, pos + p.per);
+
+    // copies: instruction j covers rows RPI j .. of the tile, piece (l % PPR) ^ swz(row)
+    const int c_row = lane / PPR;
+    constexpr int PJ = RPI >= 16 ? 1 : 16 / RPI;  // the swizzles repeat every 16 rows
+    uint32_t k_off[PJ], v_offg[PJ];
+#pragma unroll
+    for (int j = 0; j < PJ; ++j) {
+        k_off[j] = (uint32_t)(((lane % PPR) ^ k_swz<D>(c_row + j * RPI)) * 16);
+        v_offg[j] = (uint32_t)(((lane % PPR) ^ v_swz<D>(c_row + j * RPI)) * 16);
+    }
+    char* ring = smem + wave * 2 * SLOT;
+    const uint32_t ring_addr = lds_addr32(ring);
+    const uint32_t last = (uint32_t)(p.Lk - 1);
+    int k_rd[DC], v_off[DB];
+#pragma unroll
+    for (int c = 0; c < DC; ++c) k_rd[c] = i * ROW + (((4 * c + G) ^ k_swz<D>(i)) << 4);
+    const int vr = 4 * G + (i >> 2);
+#pragma unroll
+    for (int b = 0; b < DB; ++b) v_off[b] = vr * ROW + (i & 3) * 8 + 32 * (b ^ (v_swz<D>(vr) >> 1));
+    const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+
+    while (pos < end) {
+        const int h = (int)(pos / p.units), u0 = (int)(pos - (int64_t)h * p.units);
+        const int u1 = (int)min((int64_t)p.units, u0 + (end - pos));  // this run's units of head h
+        pos += u1 - u0;
+        const uint64_t k_base = uniform_u64(K + (int64_t)h * p.Lk * D), v_base = uniform_u64(V + (int64_t)h * p.Lk * D);
+        // the wave's 32 keys of unit u; steps wholly past Lk are none of its work
+        const int kw0 = u0 * 128 + wave * 32;
+        const int n_w = kw0 < p.Lk ? min(u1 - u0, (p.Lk - 1 - kw0) / 128 + 1) : 0;
+        auto issue = [&](int s) __attribute__((always_inline)) {
+            const uint32_t dst = ring_addr + (uint32_t)((s & 1) * SLOT);
+            const uint32_t k0 = (uint32_t)(kw0 + s * 128 + c_row);
+#pragma unroll
+            for (int j = 0; j < INS; ++j) {
+                const uint32_t key = min(k0 + j * RPI, last) * (uint32_t)ROW;
+                g2lds16_stream_sb(k_base, key + k_off[j % PJ], dst + (uint32_t)(j * kChunkBytes));
+            }
+#pragma unroll
+            for (int j = 0; j < INS; ++j) {
+                const uint32_t key = min(k0 + j * RPI, last) * (uint32_t)ROW;
+                g2lds16_stream_sb(v_base, key + v_offg[j % PJ], dst + (uint32_t)(TILE + j * kChunkBytes));
+            }
+        };
+        // The first step's copies, then Q: the compiler's wait for Q (placed here by the empty
+        // statements, not in the key loop) also waits for that step, which is needed first anyway.
+        if (n_w > 0) issue(0);
+        const __bf16* Qh = Q + (int64_t)h * p.Lq * D;
+        u32x4 qf[DC];
+#pragma unroll
+        for (int c = 0; c < DC; ++c) qf[c] = ld16(Qh + (int64_t)min(i, p.Lq - 1) * D + 32 * c + 8 * G);
+#pragma unroll
+        for (int c = 0; c < DC; ++c) asm volatile("" : "+v"(qf[c]));
+
+        f32x4 acc[DB], accl = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < DB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float mref = -__builtin_inff();
+        for (int s = 0; s < n_w; ++s) {
+            wait_lgkm0();  // the reads of step s - 1, whose slot the next copies take
+            asm volatile("" ::: "memory");
+            issue(s + 1);  // past the last step: a slot that is not read (rows clamped)
+            wait_vmcnt_asm<2 * INS>();
+            const char* kb = ring + (s & 1) * SLOT;
+            f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int c = 0; c < DC; ++c)
+#pragma unroll
+                for (int b4 = 0; b4 < 2; ++b4)
+                    st[b4] = mfma_chunk<__bf16>(lds_ld16(lds_ptr((char*)kb + b4 * 16 * ROW + k_rd[c])), qf[c], st[b4]);
+            const int k0 = kw0 + s * 128;
+            if (k0 + 32 > p.Lk) {
+#pragma unroll
+                for (int b4 = 0; b4 < 2; ++b4)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (k0 + 16 * b4 + 4 * G + e >= p.Lk) st[b4][e] = -__builtin_inff();
+            }
+            float tmax = st[0][0];
+#pragma unroll
+            for (int b4 = 0; b4 < 2; ++b4)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) tmax = __builtin_fmaxf(tmax, st[b4][e]);
+            // the reference rises only where some lane's own maximum exceeds it by more than 8
+            if (__any(tmax * p.sl2 > mref + 8.0f)) {
+                const float tmax2 = max_lane_groups(tmax) * p.sl2;
+                const bool raise = tmax2 > mref + 8.0f;
+                const float mnew = raise ? tmax2 : mref;
+                const float alpha = __builtin_amdgcn_exp2f(raise ? mref - mnew : 0.f);
+                mref = mnew;
+#pragma unroll
+                for (int b = 0; b < DB; ++b) acc[b] *= alpha;
+                accl *= alpha;
+            }
+            const float nb = mref == -__builtin_inff() ? 0.f : -mref;
+            float e8[8];
+#pragma unroll
+            for (int b4 = 0; b4 < 2; ++b4)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    e8[4 * b4 + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[b4][e], p.sl2, nb));
+            const u32x4 pf = {pack_bf16(e8[0], e8[1]), pack_bf16(e8[2], e8[3]), pack_bf16(e8[4], e8[5]),
+                              pack_bf16(e8[6], e8[7])};
+            const char* vb = kb + TILE;
+#pragma unroll
+            for (int b = 0; b < DB; ++b) {
+                const uint2 lo = lds_tr16(vb + v_off[b]), hi = lds_tr16(vb + v_off[b] + 16 * ROW);
+                acc[b] = mfma_chunk<__bf16>(u32x4{lo.x, lo.y, hi.x, hi.y}, pf, acc[b]);
+            }
+            accl = mfma_chunk<__bf16>(ones, pf, accl);
+        }
+        wait_vmcnt_asm<0>();  // the rings are reused below
+
+        // ---- the four waves' sums: wave w combines d blocks w, w + 4 (all lanes of a query
+        // hold its l and m)
+        __syncthreads();
+        f32x4* xa = reinterpret_cast<f32x4*>(smem);             // [wave][block][lane]
+        float* xl = reinterpret_cast<float*>(smem + 4 * DB * 1024);  // [wave][16] l, then m
+#pragma unroll
+        for (int b = 0; b < DB; ++b) xa[(wave * DB + b) * 64 + lane] = acc[b];
+        if (G == 0) {
+            xl[wave * 16 + i] = accl[0];
+            xl[64 + wave * 16 + i] = mref;
+        }
+        __syncthreads();
+        float m = -__builtin_inff(), l = 0.f, wt[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) m = xl[64 + w * 16 + i] > m ? xl[64 + w * 16 + i] : m;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float mw = xl[64 + w * 16 + i];
+            wt[w] = mw == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(mw - m);
+            l = __builtin_fmaf(wt[w], xl[w * 16 + i], l);
+        }
+        const bool whole = u0 == 0 && u1 == p.units;
+        const int f = p.first_wg(h);
+        float* prow = part + ((p.first_slot(h, f) + (p.nsplit ? u0 / p.per : wg - f)) * p.Lq + i) * PR;
+#pragma unroll
+        for (int bb = 0; bb < DB / 4; ++bb) {
+            const int b = wave + 4 * bb;
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const f32x4 x = xa[(w * DB + b) * 64 + lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(wt[w], x[e], v[e]);
+            }
+            if (i < p.Lq) {
+                if (whole) {  // the single deferred division, one rounding to bf16
+                    const float inv = 1.0f / l;
+                    uint2 o;
+                    o.x = pack_bf16(v[0] * inv, v[1] * inv);
+                    o.y = pack_bf16(v[2] * inv, v[3] * inv);
+                    *reinterpret_cast<uint2*>(out + ((int64_t)h * p.Lq + i) * D + b * 16 + 4 * G) = o;
+                } else {
+                    *reinterpret_cast<f32x4*>(prow + b * 16 + 4 * G) = v;
+                }
+            }
+        }
+        if (!whole && wave == 0 && G == 0 && i < p.Lq) {
+            prow[D] = l;
+            prow[D + 1] = m;
+        }
+        __syncthreads();  // the exchange area is the rings' again
+    }
+}
+
+// Merge of the split heads' partials, one wave per query row: 64 partials at a time, lane g
+// holding partial g's l and m, then every lane D / 64 columns, 8 partials in flight.
+template <int D>
+__global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ part, DecodeArgs p,
+                                                              __bf16* __restrict__ out) {
+    constexpr int PR = D + 4, PER = D / 64;
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= rows) return;
-    const float* pr = part + row * nsplit * (D + 4);
-    float m = -__builtin_inff();
-    for (int g = 0; g < nsplit; ++g) m = __builtin_fmaxf(m, pr[g * (D + 4) + D + 1]);
-    float l = 0.f, acc[PER];
+    if (row >= p.BH * p.Lq) return;
+    const int h = (int)(row / p.Lq), f = p.first_wg(h), n = p.parts(h, f);
+    if (n == 1) return;  // written by the workgroup that read the whole head
+    const int64_t stride = (int64_t)p.Lq * PR;  // between the head's partials
+    const float* pr = part + (p.first_slot(h, f) * p.Lq + row % p.Lq) * PR;
+    float m = -__builtin_inff(), l = 0.f, acc[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) acc[j] = 0.f;
-    for (int g = 0; g < nsplit; ++g) {
-        const float* pg = pr + g * (D + 4);
-        const float w = __builtin_amdgcn_exp2f(pg[D + 1] - m);
-        l = __builtin_fmaf(w, pg[D], l);
+    for (int g0 = 0; g0 < n; g0 += 64, pr += 64 * stride) {
+        const int ng = min(64, n - g0);
+        const float* mine = pr + min(lane, ng - 1) * stride + D;
+        const float lg = mine[0], mg = mine[1];
+        float mn = mg;
 #pragma unroll
-        for (int j = 0; j < PER; ++j) acc[j] = __builtin_fmaf(w, pg[lane + 64 * j], acc[j]);
+        for (int o = 32; o >= 1; o >>= 1) mn = __builtin_fmaxf(mn, __shfl_xor(mn, o));
+        mn = __builtin_fmaxf(m, mn);
+        const float w = lane < ng ? __builtin_amdgcn_exp2f(mg - mn) : 0.f;
+        const float old = g0 ? __builtin_amdgcn_exp2f(m - mn) : 0.f;
+        l = __builtin_fmaf(l, old, wave_sum(w * lg));
+        m = mn;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) acc[j] *= old;
+        for (int g = 0; g < ng; g += 8) {
+            float x[8][PER];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int j = 0; j < PER; ++j) x[k][j] = pr[min(g + k, ng - 1) * stride + lane + 64 * j];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float wk = __shfl(w, min(g + k, 63));
+                if (g + k < ng)
+#pragma unroll
+                    for (int j = 0; j < PER; ++j) acc[j] = __builtin_fmaf(wk, x[k][j], acc[j]);
+            }
+        }
     }
     const float inv = 1.0f / l;
 #pragma unroll
     for (int j = 0; j < PER; ++j) out[row * D + lane + 64 * j] = (__bf16)(acc[j] * inv);
 }
 
-// Decode kernel: one wave of 16 query slots per workgroup (Lq <= 16), 128-key steps, a
-// ring of 2 slots (the next step's copies in flight while one is computed): 1024 d
-// bytes of LDS.  Measured on 256 heads x 8192 keys, d = 128, per call:
-// 157 us, against 164 us for 3 slots of 64 keys, 167 us for 2 of 64 and 173 us for
-// 4 of 32 -- fewer, larger copies in flight per workgroup stream best.
-constexpr int kDecNS = 2, kDecBKV = 128;
-constexpr int64_t kCUs = 256, kLdsPerCU = 160 * 1024;
-inline int64_t decode_lds_bytes(int64_t d) { return (int64_t)kDecNS * 2 * kDecBKV * d * 2; }
-
-// Decode split: as many workgroups as fit on the chip at once (LDS-bound: 1 per CU at
-// d = 128, 2 at d = 64), spread over the heads; each split a whole number of steps.
-// One resident round beats 2 and 4 rounds (their tails).
-static void attention_decode_split(int64_t BH, int64_t Lk, int64_t d, int* nsplit, int64_t* kchunk) {
-    const int64_t wgs = kCUs * (kLdsPerCU / decode_lds_bytes(d));
-    const int64_t steps = (Lk + kDecBKV - 1) / kDecBKV;
-    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(steps, (wgs + BH - 1) / BH));
-    const int64_t per = (steps + want - 1) / want;  // steps per split
-    *kchunk = per * kDecBKV;
-    *nsplit = (int)((Lk + *kchunk - 1) / *kchunk);
+// Workgroups of one resident round: 128 KiB of LDS at d = 128 (1 per CU), 64 KiB at d = 64 (2).
+static int64_t decode_resident(int64_t d) { return d == 64 ? 512 : 256; }
+// Runs across heads: `per` units each; fewer than 2 x 256 (d = 128) or 2 x 512 (d = 64) partial
+// slots, none where every run is whole heads.
+struct DecodePlan {
+    int64_t units, per, wgs, slots;
+    int nsplit;
+};
+static DecodePlan decode_plan(int64_t BH, int64_t Lk, int64_t d) {
+    DecodePlan p;
+    p.units = (Lk + 127) / 128;
+    const int64_t total = BH * p.units;
+    p.per = (total + decode_resident(d) - 1) / decode_resident(d);
+    p.wgs = (total + p.per - 1) / p.per;
+    p.nsplit = p.units % p.per == 0 ? (int)(p.units / p.per) : 0;  // runs that end with each head
+    p.slots = p.per % p.units == 0 ? 0 : p.nsplit ? BH * p.nsplit : p.per > p.units ? 2 * p.wgs : BH + p.wgs;
+    return p;
+}
+// The same number of runs for every head (the layout smaller workspaces were sized for).
+static int64_t decode_uniform(int64_t BH, int64_t Lk, int64_t d, int64_t* per) {
+    const int64_t units = (Lk + 127) / 128, w = decode_resident(d);
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(units, (w + BH - 1) / BH));
+    *per = (units + want - 1) / want;
+    return (units + *per - 1) / *per;
+}
+static size_t slots_bytes(int64_t slots, int64_t Lq, int64_t d) {
+    return (size_t)slots * (size_t)Lq * (size_t)(d + 4) * sizeof(float);
+}
+size_t attention_decode_least_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d) {
+    int64_t per;
+    return slots_bytes(BH * decode_uniform(BH, Lk, d, &per), Lq, d);
+}
+size_t attention_decode_workspace_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d) {
+    return std::max(attention_decode_least_bytes(BH, Lq, Lk, d), slots_bytes(decode_plan(BH, Lk, d).slots, Lq, d));
 }
 
 template <int D>
-static hipError_t run_attention_decode(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq,
-                                       int64_t Lk, float scale, float* part, void* out, hipStream_t s) {
-    int nsplit;
-    int64_t kchunk;
-    attention_decode_split(BH, Lk, D, &nsplit, &kchunk);
-    if (nsplit == 1) {  // enough heads to fill the chip: one pass, the division in the kernel's epilogue
-        attention_kernel<D, 1, 1, kDecNS, kDecBKV, true><<<dim3((unsigned)BH), 64, 0, s>>>(
-            (const __bf16*)Q, (const __bf16*)K, (const __bf16*)V, Lq, Lk, 0, scale * fa::kLog2e, 1, 1, Lk,
-            nullptr, (__bf16*)out, 1);
-        return hipGetLastError();
-    }
-    attention_kernel<D, 1, 1, kDecNS, kDecBKV, true><<<dim3((unsigned)(BH * nsplit)), 64, 0, s>>>(
-        (const __bf16*)Q, (const __bf16*)K, (const __bf16*)V, Lq, Lk, 0, scale * fa::kLog2e, 1, nsplit, kchunk,
-        part, nullptr, 1);
-    const int64_t rows = BH * Lq;
-    attention_merge_kernel<D><<<dim3((unsigned)((rows + 3) / 4)), 256, 0, s>>>(part, nsplit, rows, (__bf16*)out);
+static hipError_t run_decode(const void* Q, const void* K, const void* V, const DecodeArgs& a, int64_t wgs, bool split,
+                             void* part, void* out, hipStream_t s) {
+    attention_kernel<D><<<dim3((unsigned)wgs), 256, 0, s>>>((const __bf16*)Q, (const __bf16*)K, (const __bf16*)V, a,
+                                                           (float*)part, (__bf16*)out);
+    if (split)
+        attention_merge_kernel<D><<<dim3((unsigned)((a.BH * a.Lq + 3) / 4)), 256, 0, s>>>((const float*)part, a,
+                                                                                          (__bf16*)out);
     return hipGetLastError();
 }
 
-size_t attention_decode_workspace_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d) {
-    int nsplit;
-    int64_t kchunk;
-    attention_decode_split(BH, Lk, d, &nsplit, &kchunk);
-    return (size_t)BH * (size_t)Lq * (size_t)nsplit * (size_t)(d + 4) * sizeof(float);
-}
-
 hipError_t launch_attention_decode(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq, int64_t Lk,
-                                   int64_t d, float scale, void* workspace, void* out, hipStream_t s) {
-    if (d == 64) return run_attention_decode<64>(Q, K, V, BH, Lq, Lk, scale, (float*)workspace, out, s);
-    return run_attention_decode<128>(Q, K, V, BH, Lq, Lk, scale, (float*)workspace, out, s);
+                                   int64_t d, float scale, void* workspace, size_t workspace_bytes, void* out,
+                                   hipStream_t s) {
+    const DecodePlan plan = decode_plan(BH, Lk, d);
+    DecodeArgs a{};
+    a.BH = BH;
+    a.Lq = (int)Lq;
+    a.Lk = (int)Lk;
+    a.units = (int)plan.units;
+    a.sl2 = scale * fa::kLog2e;
+    int64_t wgs = plan.wgs;
+    a.per = (int)plan.per;
+    a.nsplit = plan.nsplit;
+    bool split = plan.slots > 0;
+    if (slots_bytes(plan.slots, Lq, d) > workspace_bytes) {
+        int64_t per;
+        a.nsplit = (int)decode_uniform(BH, Lk, d, &per);
+        a.per = (int)per;
+        wgs = BH * a.nsplit;
+        split = a.nsplit > 1;
+    }
+    if (d == 64) return run_decode<64>(Q, K, V, a, wgs, split, workspace, out, s);
+    return run_decode<128>(Q, K, V, a, wgs, split, workspace, out, s);
 }
 
 // ---------------------------------------------------------------------------
-// Allocation-free decode: the per-split partials go to a file-scope device array
-// instead of a caller workspace.  Every valid call fits it: with nsplit > 1 the
-// heads number fewer than the resident workgroups W (512 at d = 64, 256 at
-// d = 128), so BH * nsplit < 2 W and the partials take less than
-// 2 W * 16 * (d + 4) * 4 bytes -- 4.25 MiB at d = 64, 4.125 MiB at d = 128.
-// In host code `scratch` names a host-side stand-in; its device address (one
-// copy per GPU) is looked up once per device with hipGetSymbolAddress and only
-// that address is passed to kernels.
+// Allocation-free decode: the partials go to a file-scope device array instead of a caller
+// workspace.  Every call fits it: fewer than 2 W partial slots (W resident workgroups, 512 at
+// d = 64, 256 at d = 128), 4.25 MiB at d = 64 and 4.125 MiB at d = 128.  In host code `scratch`
+// names a host-side stand-in; its device address (one copy per GPU) is looked up once per device with
+// hipGetSymbolAddress and only that address is passed to kernels.
 static __device__ __align__(256) float scratch[kDecodeScratchBytes / sizeof(float)];
 
 static hipError_t decode_scratch_address(void** out) {
@@ -932,20 +909,17 @@ static hipError_t decode_scratch_address(void** out) {
 }
 
 size_t attention_decode_partials_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d) {
-    int nsplit;
-    int64_t kchunk;
-    attention_decode_split(BH, Lk, d, &nsplit, &kchunk);
-    return nsplit == 1 ? 0 : (size_t)BH * (size_t)Lq * (size_t)nsplit * (size_t)(d + 4) * sizeof(float);
+    int64_t per;
+    const int64_t n = decode_uniform(BH, Lk, d, &per);
+    return n == 1 ? 0 : slots_bytes(BH * n, Lq, d);
 }
 
 hipError_t launch_attention_decode_noalloc(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq,
                                            int64_t Lk, int64_t d, float scale, void* out, hipStream_t s) {
     void* part = nullptr;
-    if (attention_decode_partials_bytes(BH, Lq, Lk, d) > 0) {
-        const hipError_t e = decode_scratch_address(&part);
-        if (e != hipSuccess) return e;
-    }
-    return launch_attention_decode(Q, K, V, BH, Lq, Lk, d, scale, part, out, s);
+    const hipError_t e = decode_scratch_address(&part);
+    if (e != hipSuccess) return e;
+    return launch_attention_decode(Q, K, V, BH, Lq, Lk, d, scale, part, kDecodeScratchBytes, out, s);
 }
 
 // Query rows per workgroup of the prefill layouts (every layout's key step covers 128 keys).

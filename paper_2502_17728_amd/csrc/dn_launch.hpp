@@ -90,12 +90,15 @@ hipError_t launch_attention_deferred(const void* Q, const void* K, const void* V
                                      int64_t Lk, int64_t d, int causal, float scale, void* out, hipStream_t s,
                                      int group = 1);
 
-// Decode attention (Lq <= 16, all Lk keys visible): key ranges split over workgroups
-// (partials in `workspace`, attention_decode_workspace_bytes of them), then one merge;
-// a single pass straight to `out` when the heads alone fill the chip.
+// Decode attention (Lq <= 16, all Lk keys visible): the keys of all heads dealt evenly to one
+// resident round of workgroups; a head read by several leaves partials in `workspace` that a
+// merge kernel combines.  attention_decode_workspace_bytes of workspace give the even deal;
+// from attention_decode_least_bytes on every head is cut into equally many runs instead.
 size_t attention_decode_workspace_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d);
+size_t attention_decode_least_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d);
 hipError_t launch_attention_decode(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq, int64_t Lk,
-                                   int64_t d, float scale, void* workspace, void* out, hipStream_t s);
+                                   int64_t d, float scale, void* workspace, size_t workspace_bytes, void* out,
+                                   hipStream_t s);
 
 // The same with the partials in a library-owned device array of kDecodeScratchBytes per GPU
 // (no workspace argument, no allocation).  attention_decode_partials_bytes: the bytes of
