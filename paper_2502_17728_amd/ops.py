@@ -109,7 +109,7 @@ def _dev(t: Optional[torch.Tensor], name: str):
         raise ValueError(f"{name} must be a GPU tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _expect(t: Optional[torch.Tensor], name: str, shape=None, dtype=None, device=None, numel=None):
@@ -120,7 +120,7 @@ def _expect(t: Optional[torch.Tensor], name: str, shape=None, dtype=None, device
         return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
-    if shape is not None:
+    if shape is not None and t.shape != shape:
         ok = t.dim() == len(shape) and all(s is None or int(a) == int(s) for a, s in zip(t.shape, shape))
         if not ok:
             want = "[" + ", ".join("*" if s is None else str(int(s)) for s in shape) + "]"
@@ -136,10 +136,19 @@ def _expect(t: Optional[torch.Tensor], name: str, shape=None, dtype=None, device
 _TORCH_DT = {DN_F32: torch.float32, DN_BF16: torch.bfloat16}
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+def _stream(stream) -> int:
+    if stream is None:  # the current device's current stream, without building a Stream object
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+# The wrappers below run on every token of a decode loop, where the kernels take 5-20 us: a
+# call's checks are one comparison each in the usual case, and _expect, which words the error,
+# runs only where one fails.
+def _like(t: Optional[torch.Tensor], shape, x: torch.Tensor) -> bool:
+    """t is None, or has this shape and x's dtype and device."""
+    return t is None or (isinstance(t, torch.Tensor) and t.shape == shape and t.dtype == x.dtype
+                         and t.get_device() == x.get_device())
 
 
 def _check(fn: str, status: int):
@@ -153,7 +162,11 @@ def _check_rows(x: torch.Tensor, w, out: Optional[torch.Tensor], stats: Optional
         raise TypeError("w must come from ln_linear_prepare / swiglu_prepare")
     if x.dim() != 2:
         raise ValueError(f"x has shape {list(x.shape)}, expected [M, {w.K}]")
-    M = x.shape[0]
+    M, K = x.shape
+    desc = w.desc
+    if (K == desc.K and x.dtype == _TORCH_DT.get(desc.dtype) and x.is_cuda and x.get_device() == w.packed.get_device()
+            and stats is None and _like(out, (M, desc.N), x)):
+        return M
     _expect(x, "x", (M, w.K), _TORCH_DT.get(w.desc.dtype), w.packed.device)
     _expect(out, "out", (M, w.N), x.dtype, x.device)
     _expect(stats, "stats", None, torch.float32, x.device, numel=2 * M)
@@ -205,7 +218,7 @@ def ln_linear_deferred(x: torch.Tensor, w: PreparedLinear, eps: float = 1e-5,
                        out: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     M = _check_rows(x, w, out)
     if out is None:
-        out = torch.empty((M, w.N), dtype=x.dtype, device=x.device)
+        out = x.new_empty((M, w.desc.N))
     _check("ln_linear_deferred", _lib.ln_linear_deferred(
         _dev(x, "x"), ctypes.byref(w.desc), M, eps, _dev(out, "out"), _stream(stream)))
     return out
@@ -271,7 +284,7 @@ def rms_linear_deferred(x: torch.Tensor, w: PreparedLinear, eps: float = 1e-5,
                         out: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     M = _check_rows(x, w, out)
     if out is None:
-        out = torch.empty((M, w.N), dtype=x.dtype, device=x.device)
+        out = x.new_empty((M, w.desc.N))
     _check("rms_linear_deferred", _lib.rms_linear_deferred(
         _dev(x, "x"), ctypes.byref(w.desc), M, eps, _dev(out, "out"), _stream(stream)))
     return out
@@ -303,7 +316,7 @@ def rms_swiglu_deferred(x: torch.Tensor, w: PreparedLinear, eps: float = 1e-5,
                         out: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     M = _check_rows(x, w, out)
     if out is None:
-        out = torch.empty((M, w.N), dtype=x.dtype, device=x.device)
+        out = x.new_empty((M, w.desc.N))
     _check("rms_swiglu_deferred", _lib.rms_swiglu_deferred(
         _dev(x, "x"), ctypes.byref(w.desc), M, eps, _dev(out, "out"), _stream(stream)))
     return out
@@ -315,10 +328,11 @@ def softmax_pv_deferred(S: torch.Tensor, V: torch.Tensor, causal: bool = False,
         raise ValueError(f"S must be [BH, Lq, Lk] and V [BH, Lk, d]; got {list(S.shape)} and {list(V.shape)}")
     BH, Lq, Lk = S.shape
     d = V.shape[-1]
-    _expect(V, "V", (BH, Lk, d), S.dtype, S.device)
-    _expect(out, "out", (BH, Lq, d), S.dtype, S.device)
+    if not (_like(V, (BH, Lk, d), S) and _like(out, (BH, Lq, d), S)):
+        _expect(V, "V", (BH, Lk, d), S.dtype, S.device)
+        _expect(out, "out", (BH, Lq, d), S.dtype, S.device)
     if out is None:
-        out = torch.empty((BH, Lq, d), dtype=S.dtype, device=S.device)
+        out = S.new_empty((BH, Lq, d))
     _check("softmax_pv_deferred", _lib.softmax_pv_deferred(
         _dev(S, "S"), _dev(V, "V"), BH, Lq, Lk, d, int(causal), _dt(S), _dev(out, "out"), _stream(stream)))
     return out
@@ -330,11 +344,13 @@ def _check_qkv(Q, K, V, out):
         raise ValueError(f"Q must be [BHq, Lq, d] and K, V [BH, Lk, d]; got {list(Q.shape)} and {list(K.shape)}")
     BHq, Lq, d = Q.shape
     BH, Lk = K.shape[0], K.shape[1]
-    _expect(K, "K", (BH, Lk, d), Q.dtype, Q.device)
-    _expect(V, "V", (BH, Lk, d), Q.dtype, Q.device)
+    if not (_like(K, (BH, Lk, d), Q) and _like(V, (BH, Lk, d), Q)):
+        _expect(K, "K", (BH, Lk, d), Q.dtype, Q.device)
+        _expect(V, "V", (BH, Lk, d), Q.dtype, Q.device)
     if BH < 1 or BHq % BH:
         raise ValueError(f"the query heads ({BHq}) must be a multiple of the key/value heads ({BH})")
-    _expect(out, "out", tuple(Q.shape), Q.dtype, Q.device)
+    if not _like(out, Q.shape, Q):
+        _expect(out, "out", tuple(Q.shape), Q.dtype, Q.device)
     return BHq, Lq, d, BH, Lk
 
 
@@ -381,16 +397,18 @@ def attention_decode_deferred(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor,
     g = BHq // BH
     if out is None:
         out = torch.empty_like(Q)
-    Q, out_k = Q.reshape(BH, g * Lq, d), out.view(BH, g * Lq, d)
+    out_k = out
+    if not (Q.is_contiguous() and out.is_contiguous()):  # contiguous ones are [BH, g * Lq, d] as they lie
+        Q, out_k = Q.reshape(BH, g * Lq, d), out.view(BH, g * Lq, d)
     Lq = g * Lq
     if scale is None:
         scale = 1.0 / float(d) ** 0.5
-    nbytes = attention_decode_workspace_bytes(BH, Lq, Lk, d)
     if workspace is None:
+        nbytes = attention_decode_workspace_bytes(BH, Lq, Lk, d)
         workspace = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=Q.device)
     _check("attention_decode_deferred", _lib.attention_decode_deferred(
         _dev(Q, "Q"), _dev(K, "K"), _dev(V, "V"), BH, Lq, Lk, d, float(scale), _dt(Q), _dev(workspace, "workspace"),
-        workspace.numel() * workspace.element_size(), _dev(out_k, "out"), _stream(stream)))
+        workspace.numel(), _dev(out_k, "out"), _stream(stream)))
     return out
 
 
@@ -406,11 +424,10 @@ def attention_decode_deferred_noalloc(Q: torch.Tensor, K: torch.Tensor, V: torch
         out = torch.empty_like(Q)
     if not (Q.is_contiguous() and out.is_contiguous()):
         raise ValueError("Q and out must be contiguous")
-    Qg, out_k = Q.view(BH, g * Lq, d), out.view(BH, g * Lq, d)
     if scale is None:
         scale = 1.0 / float(d) ** 0.5
     _check("attention_decode_deferred_noalloc", _lib.attention_decode_deferred_noalloc(
-        _dev(Qg, "Q"), _dev(K, "K"), _dev(V, "V"), BH, g * Lq, Lk, d, float(scale), _dt(Q), _dev(out_k, "out"),
+        _dev(Q, "Q"), _dev(K, "K"), _dev(V, "V"), BH, g * Lq, Lk, d, float(scale), _dt(Q), _dev(out, "out"),
         _stream(stream)))
     return out
 
