@@ -1421,7 +1421,7 @@ static bool use_skinny(int64_t M, int64_t N, int64_t K, int64_t nblocks, int dty
     if (K >= (int64_t(1) << 22)) return false;
     if (dtype == 0) return true;
     if (M <= kDecodeRows) return false;
-    return M <= 128 || skinny_estimate_us(M, K, nblocks, gated) < 0.95 * tiles_estimate_us(M, N, K, !plain);
+    return M <= 128 || skinny_estimate_us(M, K, nblocks, gated) < 0.85 * tiles_estimate_us(M, N, K, !plain);
 }
 static hipError_t run_skinny(const MainArgs& a, int64_t n_out, int dtype, bool gated, bool plain, hipStream_t s) {
     SkinnyArgs k{};
