@@ -121,10 +121,15 @@ __global__ __launch_bounds__(NW * 64) void softmax_pv_kernel(const __bf16* __res
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // logical id: XCD-contiguous; each XCD walks whole heads, longest query blocks first
-    const int t = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int h = t / nqb;
-    const int qb = causal ? (nqb - 1 - t % nqb) : (t % nqb);
+    // causal: all heads' longest query blocks first; else whole heads in a row on each XCD
+    int h, qb;
+    if (causal) {
+        longest_first(blockIdx.x, nqb, gridDim.x / nqb, h, qb);
+    } else {
+        const int t = xcd_contiguous(blockIdx.x, gridDim.x);
+        h = t / nqb;
+        qb = t % nqb;
+    }
     const int64_t q0 = (int64_t)qb * BQ;
     const int64_t kv_end = causal ? min(Lk, q0 + BQ) : Lk;
     // key group: waves kg * NQW .. kg * NQW + NQW - 1 walk global steps gs0 .. gs0 + nsteps - 1;
@@ -527,32 +532,40 @@ static hipError_t run_softmax_pv(const void* S, const void* V, int64_t BH, int64
     return hipGetLastError();
 }
 
-// 8 waves x 2 fragments (256 queries per workgroup), two V slots and two S
-// slots per wave: 80 KiB (d = 64) or 96 KiB (d = 128) of LDS.  Deeper rings
-// measured no faster on the causal 32 x 8192 x 8192, d = 128 workload.
-constexpr int kSmWaves = 8, kSmFrags = 2, kSmStages = 2, kSmPrefetch = 2;
-// Where 256-query blocks would give fewer workgroups than the chip has CUs
-// (12 heads x 512 queries: 24), the work is latency-bound: 2 waves x 1
-// fragment (32 queries per workgroup) spread it over 8x more workgroups, with
-// rings 4 (d = 64, 48 KiB) or 3 (d = 128, 60 KiB) steps deep.
-constexpr int64_t kSmCUs = 256;
-
+// Layouts, all with two V and two S slots (deeper rings measured no faster), by the number of
+// workgroups they give.  8 waves x 2 fragments (256 queries, 96 KiB of LDS at d = 128) read V
+// least and are best once they fill the chip; 8 x 1 (128 queries) and 4 x 1 (64 queries) give
+// 2 and 4 times the workgroups, two and more to a CU; where even those are few and the keys
+// short, 32 queries with the keys split two ways inside the workgroup.  Measured (us, 256 / 128
+// / 64 queries / split):
+//   full    27 x 5536, d128 443 / 431 / 499 / 583    10 x 4200, d128 127 / 128 / 132 / 158
+//           16 x 2048, d128  51 /  37 /  41 /  54    32 x 1000, d128  34 / 24.5 / 27 / 37
+//           20 x 3000, d64  105 / 103 / 110 / 132    12 x 512, d64    15 / 10.0 / 8.9 / 7.8
+//   causal  32 x 8192, d128 454 / 496 / 496          29 x 7104, d128 349 / 425 / 616
+//           15 x 6240, d128 185 / 181 / 223          16 x 2048, d128  49 / 34.5 / 34.5
+//           8 x 8192, d64   146 / 122 / 120          11 x 728, d128   24 / 15.3 / 13.2
 hipError_t launch_softmax_pv_deferred(const void* S, const void* V, int64_t BH, int64_t Lq, int64_t Lk, int64_t d,
                                       int causal, void* out, hipStream_t s) {
-    const bool small = BH * ((Lq + 255) / 256) < kSmCUs;
-    // small and non-causal with more than one key step: two key groups per workgroup, each
-    // walking half the steps with 2-deep rings, merged in LDS (12 x 512 x 512, d64, graph
-    // replays: 6.8 us unsplit, 5.4 us split; 3- and 4-deep rings 5.7-6.0 us, one query wave
-    // per group 6.3-6.5 us)
-    const bool split = small && !causal && Lk > 64;
-    if (d == 64) {
-        if (split) return run_softmax_pv<64, 4, 1, 2, 2, 2>(S, V, BH, Lq, Lk, causal, out, s);
-        if (small) return run_softmax_pv<64, 2, 1, 4, 4>(S, V, BH, Lq, Lk, causal, out, s);
-        return run_softmax_pv<64, kSmWaves, kSmFrags, kSmStages, kSmPrefetch>(S, V, BH, Lq, Lk, causal, out, s);
+    const int64_t n256 = BH * ((Lq + 255) / 256), n128 = BH * ((Lq + 127) / 128);
+    enum { k256, k128, k64, kSplit } layout;
+    if (causal)
+        layout = n256 > 512 ? k256 : n256 > 160 ? k128 : k64;
+    else if (n128 > 256)
+        layout = k256;
+    else if (n128 > 160)
+        layout = k128;
+    else
+        layout = Lk > 64 && Lk <= 1024 ? kSplit : k64;
+#define DN_SOFTMAX_LAYOUT(...)                                                              \
+    (d == 64 ? run_softmax_pv<64, __VA_ARGS__>(S, V, BH, Lq, Lk, causal, out, s)            \
+             : run_softmax_pv<128, __VA_ARGS__>(S, V, BH, Lq, Lk, causal, out, s))
+    switch (layout) {
+        case k256: return DN_SOFTMAX_LAYOUT(8, 2, 2, 2);
+        case k128: return DN_SOFTMAX_LAYOUT(8, 1, 2, 2);
+        case k64: return DN_SOFTMAX_LAYOUT(4, 1, 2, 2);
+        default: return DN_SOFTMAX_LAYOUT(4, 1, 2, 2, 2);
     }
-    if (split) return run_softmax_pv<128, 4, 1, 2, 2, 2>(S, V, BH, Lq, Lk, causal, out, s);
-    if (small) return run_softmax_pv<128, 2, 1, 3, 3>(S, V, BH, Lq, Lk, causal, out, s);
-    return run_softmax_pv<128, kSmWaves, kSmFrags, kSmStages, kSmPrefetch>(S, V, BH, Lq, Lk, causal, out, s);
+#undef DN_SOFTMAX_LAYOUT
 }
 
 }  // namespace dn
