@@ -104,7 +104,8 @@ DN_API dn_status ln_linear_prepare(const void* W, const void* gamma, const void*
  * centering (I - E/n) applied as  x(I - E/n)W' = xW' - mean 1 W').
  * mean and the biased variance follow Eq. (1); rstd = 1/sqrt(var + eps) as
  * in Eq. (2).  eps must be finite and >= 0.  x and out have w->dtype.
- * On the large-tile kernels (more than 128 rows, K % 64 == 0) the
+ * On the large-tile kernels (bf16, K % 64 == 0, more than 128 rows unless the
+ * few-row kernel is clearly the faster) the
  * workgroups that share a 256-row block split the reduction of its moments
  * and exchange the sums through the library's mailbox; a workgroup that does
  * not find a peer's sums within 200 us (a peer not resident on a busy GPU)

@@ -1400,9 +1400,11 @@ static void decode_dispatch(int64_t nblocks, F&& launch) {  // ceil(nblocks / 25
 // The streamed few-row kernel against the tiles.  Up to 128 rows it always runs (4096 -> 12288
 // at 24 / 50 / 100 rows 21 / 24 / 32 us, where the decode layout with 2 - 8 row fragments per
 // wave took 24 / 38 / 55 us on the same card; 8192 -> 28672 at 60 / 100 rows 79 / 95 against
-// 125 / 144 us).  Past that it runs where its estimate is below the tiles' (us, same cards):
+// 125 / 144 us).  Past that it runs where its estimate is below 0.85 of the tiles' (us, same cards):
 // 200 rows 4096 -> 12288 43 / 63, 313 and 500 rows 4096 -> 6144 35 / 58 and 40 / 59, 300 rows
 // 768 -> 3072 9 / 17; at 1000 rows 4096 -> 12288 it would take 151 against 105.
+// The 0.85 covers the error of the two estimates: at 0.95, 5233 rows of 752 -> 1176 came here
+// and took 28.9 us instead of 27.2.
 // Tiles, per 64 k: 128 x 128 in one round 0.83 us, 256 x 256 1.3 us (1.6 us with the chip full
 // and its clock down), the two-stage 128 x 128 loop 1.6 us alone and 1.9 us two to a CU.
 static double tiles_estimate_us(int64_t M, int64_t N, int64_t K, bool grouped) {
