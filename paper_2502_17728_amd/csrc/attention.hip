@@ -783,8 +783,9 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) mn = __builtin_fmaxf(mn, __shfl_xor(mn, o));
         mn = __builtin_fmaxf(m, mn);
-        const float w = lane < ng ? __builtin_amdgcn_exp2f(mg - mn) : 0.f;
-        const float old = g0 ? __builtin_amdgcn_exp2f(m - mn) : 0.f;
+        // partials whose scores are all -inf (m = -inf) weigh nothing, also while mn is -inf still
+        const float w = lane < ng && mg != -__builtin_inff() ? __builtin_amdgcn_exp2f(mg - mn) : 0.f;
+        const float old = m != -__builtin_inff() ? __builtin_amdgcn_exp2f(m - mn) : 0.f;
         l = __builtin_fmaf(l, old, wave_sum(w * lg));
         m = mn;
 #pragma unroll

@@ -47,3 +47,23 @@ def test_deal(BH, Lq, Lk, d):
     out = ops.attention_decode_deferred(q, k, v, scale=case["scale"], workspace=ws[:least])
     _check(case, out, BH, Lq, d)
     assert (ws[least:] == 0xff).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hidden", [range(0, 8192), range(0, 8200), range(4096, 11000)])
+def test_runs_of_minus_infinite_scores(d, hidden):
+    # whole partials (of 128 keys: one head gives more than 64) whose scores are all -inf weigh
+    # nothing, wherever they lie; a row with no other score is NaN
+    from paper_2502_17728_amd import ops
+    case = I.make_decode_case(1, 2, 11000, d, seed=d)
+    q, k, v = case["Q"].clone(), case["K"].clone(), case["V"]
+    q[:, :, 0] = 1.0
+    hid = torch.zeros(11000, dtype=torch.bool)
+    hid[list(hidden)] = True
+    k[:, hid, 0] = float("-inf")
+    ref = oracle.attention(q.reshape(-1, d), k[:, ~hid], v[:, ~hid], case["scale"], head=np.zeros(2, int))
+    for f in (ops.attention_decode_deferred, ops.attention_decode_deferred_noalloc):
+        got = f(cuda(q), cuda(k), cuda(v), scale=case["scale"]).cpu().reshape(-1, d)
+        assert rowwise_rel_err(got, ref) <= TOL[torch.bfloat16]
+    k[:, :, 0] = float("-inf")
+    assert torch.isnan(ops.attention_decode_deferred(cuda(q), cuda(k), cuda(v), scale=case["scale"])).all()
