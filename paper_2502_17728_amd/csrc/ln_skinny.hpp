@@ -146,8 +146,11 @@ __global__ __launch_bounds__(RF* KH* kWave) void ln_skinny_kernel(
     auto compute = [&](Frags& f, int s, auto tail) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < CPW; ++u) {
-            if constexpr (decltype(tail)::value)  // the last stage may reach past K
-                f[u][0] = (int64_t)(s * CH + kh + u * KH) * KC + G * EPL < K ? f[u][0] : zero;
+            if constexpr (decltype(tail)::value) {  // the last stage may reach past K
+                const int ch = s * CH + kh + u * KH;
+                if (ch >= (int)kchunks) continue;  // a repeated W' chunk: 0 times an infinite weight is NaN
+                f[u][0] = (int64_t)ch * KC + G * EPL < K ? f[u][0] : zero;
+            }
             if constexpr (F32) {  // a chunk is four dependent products per block: the blocks' chains interleave
 #pragma unroll
                 for (int j = 0; j < 4; ++j)

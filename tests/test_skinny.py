@@ -100,3 +100,20 @@ def test_fp32(M, K, N):
     w = ops.swiglu_prepare(cuda(g["Wg"]), cuda(g["Wu"]), cuda(g["gamma"]))
     out = ops.rms_swiglu_deferred(cuda(g["x"]), w, g["eps"])
     assert rowwise_rel_err(out.cpu(), oracle.rms_swiglu(g["x"], g["gamma"], g["Wg"], g["Wu"], g["eps"])) <= tol
+
+
+@pytest.mark.parametrize("M,K,dtype", [(3, 8, "f32"), (40, 24, "f32"), (300, 72, "f32"), (20, 8, "bf16"), (40, 40, "bf16"),
+                                       (100, 328, "bf16"), (300, 200, "bf16")])
+def test_infinite_weight_in_the_last_chunk(M, K, dtype):
+    # an infinite weight of the last k row, where the last stage of chunks reaches past K: +-inf as the
+    # plain product gives, in its column only
+    from paper_2502_17728_amd import ops
+    c = I.make_ln_case(M, K, 136, dtype, seed=M)
+    W = c["W"].clone()
+    W[K - 1, 5] = float("inf")
+    out = ops.gemm(cuda(c["x"]), ops.ln_linear_prepare(cuda(W), torch.ones(K, dtype=W.dtype, device="cuda"))).cpu()
+    x_last = c["x"][:, K - 1].float()
+    assert (x_last != 0).all()
+    assert torch.equal(out[:, 5].float(), torch.sign(x_last) * float("inf"))
+    keep = [n for n in range(136) if n != 5]
+    assert rowwise_rel_err(out[:, keep], (oracle.to_f64(c["x"]) @ oracle.to_f64(c["W"]))[:, keep]) <= TOL[W.dtype]
