@@ -6,6 +6,7 @@
 
 #include "dn.h"
 #include "dn_launch.hpp"
+#include "launch_rules.hpp"
 
 namespace {
 

@@ -40,6 +40,7 @@
 
 #include "dn_device.hpp"
 #include "dn_launch.hpp"
+#include "launch_rules.hpp"
 
 namespace dn {
 namespace fa {
@@ -810,42 +811,6 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
     for (int j = 0; j < PER; ++j) out[row * D + lane + 64 * j] = (__bf16)(acc[j] * inv);
 }
 
-// Workgroups of one resident round: 128 KiB of LDS at d = 128 (1 per CU), 64 KiB at d = 64 (2).
-static int64_t decode_resident(int64_t d) { return d == 64 ? 512 : 256; }
-// Runs across heads: `per` units each; fewer than 2 x 256 (d = 128) or 2 x 512 (d = 64) partial
-// slots, none where every run is whole heads.
-struct DecodePlan {
-    int64_t units, per, wgs, slots;
-    int nsplit;
-};
-static DecodePlan decode_plan(int64_t BH, int64_t Lk, int64_t d) {
-    DecodePlan p;
-    p.units = (Lk + 127) / 128;
-    const int64_t total = BH * p.units;
-    p.per = (total + decode_resident(d) - 1) / decode_resident(d);
-    p.wgs = (total + p.per - 1) / p.per;
-    p.nsplit = p.units % p.per == 0 ? (int)(p.units / p.per) : 0;  // runs that end with each head
-    p.slots = p.per % p.units == 0 ? 0 : p.nsplit ? BH * p.nsplit : p.per > p.units ? 2 * p.wgs : BH + p.wgs;
-    return p;
-}
-// The same number of runs for every head (the layout smaller workspaces were sized for).
-static int64_t decode_uniform(int64_t BH, int64_t Lk, int64_t d, int64_t* per) {
-    const int64_t units = (Lk + 127) / 128, w = decode_resident(d);
-    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(units, (w + BH - 1) / BH));
-    *per = (units + want - 1) / want;
-    return (units + *per - 1) / *per;
-}
-static size_t slots_bytes(int64_t slots, int64_t Lq, int64_t d) {
-    return (size_t)slots * (size_t)Lq * (size_t)(d + 4) * sizeof(float);
-}
-size_t attention_decode_least_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d) {
-    int64_t per;
-    return slots_bytes(BH * decode_uniform(BH, Lk, d, &per), Lq, d);
-}
-size_t attention_decode_workspace_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d) {
-    return std::max(attention_decode_least_bytes(BH, Lq, Lk, d), slots_bytes(decode_plan(BH, Lk, d).slots, Lq, d));
-}
-
 template <int D>
 static hipError_t run_decode(const void* Q, const void* K, const void* V, const DecodeArgs& a, int64_t wgs, bool split,
                              void* part, void* out, hipStream_t s) {
@@ -921,42 +886,6 @@ hipError_t launch_attention_decode_noalloc(const void* Q, const void* K, const v
     const hipError_t e = decode_scratch_address(&part);
     if (e != hipSuccess) return e;
     return launch_attention_decode(Q, K, V, BH, Lq, Lk, d, scale, part, kDecodeScratchBytes, out, s);
-}
-
-// Query rows per workgroup of the prefill layouts (every layout's key step covers 128 keys).
-constexpr int64_t kMaxPrefillGrid = (int64_t(1) << 31) - 1;
-constexpr int kPrefillBQ[4] = {256, 128, 64, 32};
-
-// Which layout.  Fewer queries per workgroup cost more per score (the K and V fragments read
-// from LDS serve fewer queries: per 128-key step at d = 128 and a full chip 3.35 us for 256
-// queries, 1.9 for 128, 1.3 for 64, 1.0 for 32), but give more workgroups and split each one's
-// keys 1, 2, 4 and 4 ways.  The time is about the larger of the longest workgroup's (its steps
-// at the lone-workgroup rate, plus a start and an end) and of all the work over 256 CUs; the
-// layout with the smallest estimate runs.  Measured, best layout against 256 queries for all
-// (graph replays, us): 8 heads x 512, d64 7.2 / 14; 32 x 1000 causal 20.9 / 29; 16 x 512
-// against 3000 keys 27 / 67; 32 x 2048 causal 45 / 51; from 32 x 4096 causal on 256 is best
-// (122 / 142 with 128).
-static int prefill_layout(int64_t BH, int64_t Lq, int64_t Lk, int64_t d, int causal) {
-    struct Cost {
-        double full, alone, ends;  // us per step with every CU busy / alone, us per workgroup
-    };
-    static constexpr Cost kCost[2][4] = {{{2.0, 1.75, 7.0}, {1.2, 1.1, 6.0}, {0.64, 0.7, 3.5}, {0.44, 0.5, 2.8}},
-                                         {{3.35, 2.5, 8.0}, {1.9, 1.55, 6.5}, {1.3, 1.1, 6.0}, {1.0, 0.88, 3.5}}};
-    int best = 0;
-    double best_t = 0;
-    for (int v = 0; v < 4; ++v) {
-        const Cost& c = kCost[d == 128][v];
-        const int64_t n = (Lq + kPrefillBQ[v] - 1) / kPrefillBQ[v], wgs = BH * n;
-        if (wgs > kMaxPrefillGrid) continue;
-        const int64_t longest = (Lk + 127) / 128;
-        const double mean = causal ? 0.5 * (double)(longest + 1) : (double)longest;
-        const double t = std::max((double)longest * c.alone + c.ends, (double)wgs * (mean * c.full + c.ends) / 256.0);
-        if (v == 0 || t < best_t) {
-            best = v;
-            best_t = t;
-        }
-    }
-    return best;
 }
 
 template <int D>

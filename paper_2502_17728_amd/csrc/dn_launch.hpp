@@ -61,7 +61,6 @@ struct SkinnyArgs {
 };
 hipError_t launch_skinny(const SkinnyArgs& a, bool gated, bool plain, hipStream_t s);      // bf16
 hipError_t launch_skinny_f32(const SkinnyArgs& a, bool gated, bool plain, hipStream_t s);  // fp32
-double skinny_estimate_us(int64_t M, int64_t K, int64_t nblocks, bool gated);
 
 // y = (x - mean) rstd gamma + beta from per-row (mean, rstd); beta nullable.
 hipError_t launch_apply_norm(const void* x, const float* stats, const void* gamma, const void* beta, int64_t M,
@@ -94,8 +93,6 @@ hipError_t launch_attention_deferred(const void* Q, const void* K, const void* V
 // resident round of workgroups; a head read by several leaves partials in `workspace` that a
 // merge kernel combines.  attention_decode_workspace_bytes of workspace give the even deal;
 // from attention_decode_least_bytes on every head is cut into equally many runs instead.
-size_t attention_decode_workspace_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d);
-size_t attention_decode_least_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d);
 hipError_t launch_attention_decode(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq, int64_t Lk,
                                    int64_t d, float scale, void* workspace, size_t workspace_bytes, void* out,
                                    hipStream_t s);

@@ -30,6 +30,7 @@
 
 #include "dn_device.hpp"
 #include "dn_launch.hpp"
+#include "launch_rules.hpp"
 
 namespace dn {
 
@@ -1272,51 +1273,12 @@ static uint32_t moment_wait_ticks() {
     return e ? (uint32_t)strtoul(e, nullptr, 10) : 20000u;
 }
 
-// Workgroups for tm x tn tiles.  Deferred LN: each workgroup takes `group` column
-// tiles of one row block and reduces the row moments once, on its first tile.
-// With one workgroup per CU the run takes about ceil(workgroups / 256) * group
-// tile times; take the group that minimises that, and of equal ones the largest
-// (fewest moment reductions).  384 tiles: group 2 (192 workgroups, 2 tile times)
-// instead of group 1 (384 workgroups, also 2 tile times, twice the moment work).
-struct TilePlan {
-    int64_t group, ngroups, wgs, times;
-};
-static TilePlan plan_tiles(int64_t tm, int64_t tn, bool grouped) {
-    int64_t group = 1;
-    if (grouped) {
-        int64_t best = -1;
-        for (int64_t g = 1; g <= tn; ++g) {
-            const int64_t span = (tm * ((tn + g - 1) / g) + 255) / 256 * g;
-            if (best < 0 || span <= best) {
-                best = span;
-                group = g;
-            }
-        }
-    }
-    const int64_t ngroups = (tn + group - 1) / group, wgs = tm * ngroups;
-    return TilePlan{group, ngroups, wgs, (wgs + 255) / 256 * group};
-}
-
-// 256 x 192 tiles where they fill the chip in fewer 256 x 256-tile times: a narrow
-// tile costs about kNarrowCost of a square one (three quarters of the MACs, a
-// little more operand traffic per MAC).  4096 x 4096 -> 6144: 512 narrow tiles in
-// two full rounds instead of 384 square ones in 1.5; 1024 x 4096 -> 12288: 256
-// instead of 192 on 256 CUs.
-constexpr double kNarrowCost = 0.8;
-
 template <Epi EPI, int BT = 256>
 static hipError_t run_pipe(const MainArgs& args, hipStream_t s) {
     MainArgs a = args;
-    const int64_t tm = (a.M + BT - 1) / BT, tn = (a.N + BT - 1) / BT;
-    TilePlan plan = plan_tiles(tm, tn, EPI != Epi::kGemm);
-    bool narrow = false;
-    if constexpr (BT == 256) {
-        const TilePlan nplan = plan_tiles(tm, (a.N + 191) / 192, EPI != Epi::kGemm);
-        if ((double)nplan.times * kNarrowCost < (double)plan.times) {
-            plan = nplan;
-            narrow = true;
-        }
-    }
+    const bool narrow = BT == 256 && use_narrow_tiles(a.M, a.N, EPI != Epi::kGemm);
+    const int64_t cols = narrow ? 192 : BT;
+    const TilePlan plan = plan_tiles((a.M + BT - 1) / BT, (a.N + cols - 1) / cols, EPI != Epi::kGemm);
     const int64_t group = plan.group, ngroups = plan.ngroups, wgs = plan.wgs;
     // Shared moments where the workgroups of a row block are co-resident (one round of
     // workgroups: 256 at one per CU, 512 for the 128 x 128 tiles at two per CU) and number
@@ -1340,29 +1302,6 @@ static hipError_t run_pipe(const MainArgs& args, hipStream_t s) {
     else
         pipe_kernel<EPI, 4, 2><<<dim3((unsigned)wgs), 8 * kWave, 0, s>>>(a, (int)group);
     return hipGetLastError();
-}
-
-// The 256x256 kernel past 128 rows (and K a multiple of its stage), where the
-// 128 x 128 tiles do not fit in one round.  Below one 256 x 256 tile per CU it
-// still beats the two-stage 128 x 128 loop, which then needs a second round of
-// tiles where the 256 x 256 kernel needs none.  Measured on 4096 -> 12288:
-// 768 and 1024 rows 89 / 97 us against 178 / 185 us; 8192 -> 28672 at 384 and
-// 512 rows 222 / 226 against 376 / 381 us, at 129-256 rows within 5 %.
-static bool use_big_tiles(int64_t M, int64_t N, int64_t K) {
-    if (N >= (int64_t(1) << 22)) return false;  // 256 output rows < 2^31 bytes (32-bit store offsets)
-    // K < 2^22 keeps the 32-bit copy offsets of a 256-row panel (256 K bf16) and of a
-    // 16-chunk-column W' panel (16 x K/32 KiB) below 4 GiB.
-    return K % 64 == 0 && K < (int64_t(1) << 22) && M > 128;
-}
-// The pipelined kernel on 128 x 128 tiles (4 waves, two workgroups per CU) while
-// those tiles number at most one per CU: then a tile takes far less than a
-// 256 x 256 one and the chip is as full.  Measured on 4096 -> 12288 at 129 / 256
-// rows (192 tiles) 56 / 58 us against 86 us on 256 x 256 tiles, on 8192 -> 28672
-// at 65 / 100 rows (224 tiles) 132 / 133 us against 174 / 184 us on the 128 x 128
-// two-stage loop; at 288 tiles and more it lost (97-448 us against 89-230 us).
-static bool use_mid_tiles(int64_t M, int64_t N, int64_t K) {
-    return K % 64 == 0 && K < (int64_t(1) << 22) && N < (int64_t(1) << 22) &&
-           ((M + 127) / 128) * ((N + 127) / 128) <= 256;
 }
 
 static MainArgs packed_args(const void* A, const void* packed, int64_t M, int64_t K, int64_t N, int dtype,
@@ -1389,7 +1328,6 @@ static MainArgs packed_args(const void* A, const void* packed, int64_t M, int64_
 // for the partial sums).  Measured on the 8192 x 28672 up-projection (1792
 // blocks, nc = 7): 78.5-78.8 us for 1-16 tokens, against 81-91 us for the
 // 4- and 8-wave layouts with 1-4 blocks per workgroup.
-constexpr int64_t kDecodeRows = 16;
 template <bool PLAIN, int NC, class F>
 static void decode_dispatch(int64_t nblocks, F&& launch) {  // ceil(nblocks / 256) column blocks, at most NC
     if constexpr (NC > 1)
@@ -1397,33 +1335,12 @@ static void decode_dispatch(int64_t nblocks, F&& launch) {  // ceil(nblocks / 25
     launch(ln_decode_bf16_kernel<16, NC, 1, false, PLAIN>, 16, NC);
 }
 
-// The streamed few-row kernel against the tiles.  Up to 128 rows it always runs (4096 -> 12288
-// at 24 / 50 / 100 rows 21 / 24 / 32 us, where the decode layout with 2 - 8 row fragments per
-// wave took 24 / 38 / 55 us on the same card; 8192 -> 28672 at 60 / 100 rows 79 / 95 against
-// 125 / 144 us).  Past that it runs where its estimate is below 0.85 of the tiles' (us, same cards):
-// 200 rows 4096 -> 12288 43 / 63, 313 and 500 rows 4096 -> 6144 35 / 58 and 40 / 59, 300 rows
-// 768 -> 3072 9 / 17; at 1000 rows 4096 -> 12288 it would take 151 against 105.
-// The 0.85 covers the error of the two estimates: at 0.95, 5233 rows of 752 -> 1176 came here
-// and took 28.9 us instead of 27.2.
-// Tiles, per 64 k: 128 x 128 in one round 0.83 us, 256 x 256 1.3 us (1.6 us with the chip full
-// and its clock down), the two-stage 128 x 128 loop 1.6 us alone and 1.9 us two to a CU.
-static double tiles_estimate_us(int64_t M, int64_t N, int64_t K, bool grouped) {
-    const double k64 = (double)K / 64.0;
-    if (use_mid_tiles(M, N, K)) return 5.0 + k64 * 0.83;
-    const int64_t tm = (M + 255) / 256;
-    if (use_big_tiles(M, N, K)) {
-        const TilePlan sq = plan_tiles(tm, (N + 255) / 256, grouped), na = plan_tiles(tm, (N + 191) / 192, grouped);
-        const double full = (sq.wgs >= 192 ? 1.6 : 1.3) * k64;
-        return 5.0 + full * std::min((double)sq.times, (double)na.times * kNarrowCost);
-    }
-    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);  // two fit a CU
-    return 5.0 + (tiles > 256 ? 1.9 : 1.6) * k64 * (double)((tiles + 511) / 512);
-}
-static bool use_skinny(int64_t M, int64_t N, int64_t K, int64_t nblocks, int dtype, bool gated, bool plain) {
-    if (K >= (int64_t(1) << 22)) return false;
-    if (dtype == 0) return true;
-    if (M <= kDecodeRows) return false;
-    return M <= 128 || skinny_estimate_us(M, K, nblocks, gated) < 0.85 * tiles_estimate_us(M, N, K, !plain);
+template <Epi EPI>
+static hipError_t run_tiles(Product kernel, const MainArgs& a, int dtype, hipStream_t s) {
+    if (dtype == 0) return hipErrorInvalidValue;  // K >= 2^22, which the prepare calls refuse
+    if (kernel == Product::kTiles128) return run_pipe<EPI, 128>(a, s);
+    if (kernel == Product::kTiles256) return run_pipe<EPI>(a, s);
+    return run_main<__bf16, 128, 128, 2, 2, BMode::kPacked, EPI>(a, 1, s);
 }
 static hipError_t run_skinny(const MainArgs& a, int64_t n_out, int dtype, bool gated, bool plain, hipStream_t s) {
     SkinnyArgs k{};
@@ -1454,7 +1371,8 @@ hipError_t launch_ln_linear_deferred(const void* x, const void* packed, int64_t 
     a.rms = rms;
     a.row_stats = row_stats;
     a.stats_out = stats_out;
-    if (dtype == 1 && M <= kDecodeRows) {
+    const Product kernel = product_kernel(M, N, K, dtype, false, false);
+    if (kernel == Product::kDecode) {
         auto launch = [&](auto kern, int ks, int cols) {
             const int64_t wgs = (a.nblocks + cols - 1) / cols;
             kern<<<dim3((unsigned)wgs), ks * kWave, 0, s>>>((const __bf16*)x, (const char*)a.B, a.kchunks,
@@ -1464,11 +1382,8 @@ hipError_t launch_ln_linear_deferred(const void* x, const void* packed, int64_t 
         decode_dispatch<false, 7>(a.nblocks, launch);
         return hipGetLastError();
     }
-    if (use_skinny(M, N, K, a.nblocks, dtype, false, false)) return run_skinny(a, N, dtype, false, false, s);
-    if (dtype == 0) return hipErrorInvalidValue;  // K >= 2^22, which the prepare calls refuse
-    if (use_mid_tiles(M, N, K)) return run_pipe<Epi::kLnDeferred, 128>(a, s);
-    if (use_big_tiles(M, N, K)) return run_pipe<Epi::kLnDeferred>(a, s);
-    return run_main<__bf16, 128, 128, 2, 2, BMode::kPacked, Epi::kLnDeferred>(a, 1, s);
+    if (kernel == Product::kStreamed) return run_skinny(a, N, dtype, false, false, s);
+    return run_tiles<Epi::kLnDeferred>(kernel, a, dtype, s);
 }
 
 bool ln_on_load_supported(int64_t M, int64_t K, int64_t N, int dtype) {
@@ -1496,7 +1411,8 @@ hipError_t launch_swiglu_deferred(const void* x, const void* packed, int64_t M, 
     a.eps = eps;
     a.rms = rms;
     a.n_out = N;
-    if (dtype == 1 && M <= kDecodeRows) {
+    const Product kernel = product_kernel(M, np, K, dtype, true, false);
+    if (kernel == Product::kDecode) {
         auto launch = [&](auto kern, int ks, int cols) {
             const int64_t wgs = (a.nblocks + cols - 1) / cols;
             kern<<<dim3((unsigned)wgs), ks * kWave, 0, s>>>((const __bf16*)x, (const char*)a.B, a.kchunks, a.nblocks,
@@ -1509,11 +1425,8 @@ hipError_t launch_swiglu_deferred(const void* x, const void* packed, int64_t M, 
         swiglu_dispatch_nc<14>(2 * std::min<int64_t>(7, std::max<int64_t>(1, (a.nblocks / 2 + 255) / 256)), launch);
         return hipGetLastError();
     }
-    if (use_skinny(M, np, K, a.nblocks, dtype, true, false)) return run_skinny(a, N, dtype, true, false, s);
-    if (dtype == 0) return hipErrorInvalidValue;  // K >= 2^22, which the prepare calls refuse
-    if (use_mid_tiles(M, np, K)) return run_pipe<Epi::kSwiGlu, 128>(a, s);
-    if (use_big_tiles(M, np, K)) return run_pipe<Epi::kSwiGlu>(a, s);
-    return run_main<__bf16, 128, 128, 2, 2, BMode::kPacked, Epi::kSwiGlu>(a, 1, s);
+    if (kernel == Product::kStreamed) return run_skinny(a, N, dtype, true, false, s);
+    return run_tiles<Epi::kSwiGlu>(kernel, a, dtype, s);
 }
 
 hipError_t launch_gemm(const void* A, const void* B, const void* bias, int64_t batch, int64_t M, int64_t K,
@@ -1535,7 +1448,8 @@ hipError_t launch_gemm(const void* A, const void* B, const void* bias, int64_t b
     a.bias = bias;
     a.a_causal = a_causal;
     if (b_layout == 2) {
-        if (dtype == 1 && M <= kDecodeRows) {
+        const Product kernel = product_kernel(M, N, K, dtype, false, true);
+        if (kernel == Product::kDecode) {
             // decode shapes: the streaming kernel of the deferred path without its moments,
             // in the same layouts (so the unfused comparison is like for like)
             auto launch = [&](auto kern, int ks, int cols) {
@@ -1548,11 +1462,8 @@ hipError_t launch_gemm(const void* A, const void* B, const void* bias, int64_t b
             decode_dispatch<true, 7>(a.nblocks, launch);
             return hipGetLastError();
         }
-        if (use_skinny(M, N, K, a.nblocks, dtype, false, true)) return run_skinny(a, N, dtype, false, true, s);
-        if (dtype == 0) return hipErrorInvalidValue;  // K >= 2^22, which the prepare calls refuse
-        if (use_mid_tiles(M, N, K)) return run_pipe<Epi::kGemm, 128>(a, s);
-        if (use_big_tiles(M, N, K)) return run_pipe<Epi::kGemm>(a, s);
-        return run_main<__bf16, 128, 128, 2, 2, BMode::kPacked, Epi::kGemm>(a, 1, s);
+        if (kernel == Product::kStreamed) return run_skinny(a, N, dtype, false, true, s);
+        return run_tiles<Epi::kGemm>(kernel, a, dtype, s);
     }
     if (dtype == 0) return run_main<float, 32, 64, 2, 2, BMode::kNK, Epi::kGemm, kF32Stages, kF32Chunks>(a, batch, s);
     if (b_layout == 1) return run_main<__bf16, 128, 128, 2, 2, BMode::kNK, Epi::kGemm>(a, batch, s);

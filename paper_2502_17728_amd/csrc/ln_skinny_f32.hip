@@ -1,4 +1,5 @@
 // ln_skinny_f32.hip -- LayerNorm/RMSNorm products on packed fp32 weights, every size.
+#include "launch_rules.hpp"
 #include "ln_skinny.hpp"
 
 namespace dn {
@@ -11,29 +12,6 @@ static hipError_t skinny_rf(int rf, const SkinnyArgs& a, hipStream_t s) {
         case 4: return run_skinny_kernel<float, 4, 2, NC, KIND>(a, s);
         default: return run_skinny_kernel<float, 8, 1, NC, KIND>(a, s);
     }
-}
-// The plan by estimated time, as for bf16 (ln_skinny.hip) with fp32's stages: 0.06 rf nc us of
-// matrix work per 64 k and 0.14 + 0.035 rf us besides.  Measured (graph replays, us; before:
-// 32 x 64 tiles of a two- to four-stage loop whose x copies were half lines): 128 rows
-// 768 -> 3072 12.6 / 15.3, 1 row 4096 -> 6144 22 / 54, 1 row 4992 -> 1104 16 / 64, 477 rows
-// 4096 -> 12288 410 / 632 (117 TFLOP/s), 1000 rows 768 -> 3072 46 / 78.
-static void plan_f32(int64_t M, int64_t K, int64_t nblocks, bool gated, int* rf_out, int* nc_out) {
-    static constexpr int kRf[4] = {1, 2, 4, 8};
-    double best = 0;
-    for (int rf : kRf)
-        for (int nc = gated ? 2 : 1; nc <= 6; nc += gated ? 2 : 1) {
-            if (nc == 5 || (rf == 1 && nc == 6)) continue;  // one row block x 6 columns: 2-deep rings only
-            const int64_t nrb = (M + 16 * rf - 1) / (16 * rf), wgs = nrb * ((nblocks + nc - 1) / nc);
-            const double w_us = (double)nblocks * 64.0 * (double)K / 6.2e6, hbm = w_us * (w_us > 38.0 ? (double)nrb : 1.0);
-            const double stage = 0.14 + 0.035 * rf + 0.06 * rf * nc;
-            const double body = (double)((wgs + 255) / 256) * (4.0 + (double)K / 64.0 * stage);
-            const double us = 1.0 + std::max(hbm + 4.0, body) + 0.15 * std::min(hbm, body);
-            if (best == 0 || us < best) {
-                best = us;
-                *rf_out = rf;
-                *nc_out = nc;
-            }
-        }
 }
 template <Skinny KIND>
 static hipError_t skinny_linear(int rf, int nc, const SkinnyArgs& a, hipStream_t s) {

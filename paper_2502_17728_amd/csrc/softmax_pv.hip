@@ -44,6 +44,7 @@
 
 #include "dn_device.hpp"
 #include "dn_launch.hpp"
+#include "launch_rules.hpp"
 
 namespace dn {
 
@@ -532,37 +533,15 @@ static hipError_t run_softmax_pv(const void* S, const void* V, int64_t BH, int64
     return hipGetLastError();
 }
 
-// Layouts, all with two V and two S slots (deeper rings measured no faster), by the number of
-// workgroups they give.  8 waves x 2 fragments (256 queries, 96 KiB of LDS at d = 128) read V
-// least and are best once they fill the chip; 8 x 1 (128 queries) and 4 x 1 (64 queries) give
-// 2 and 4 times the workgroups, two and more to a CU; where even those are few and the keys
-// short, 32 queries with the keys split two ways inside the workgroup.  Measured (us, 256 / 128
-// / 64 queries / split):
-//   full    27 x 5536, d128 443 / 431 / 499 / 583    10 x 4200, d128 127 / 128 / 132 / 158
-//           16 x 2048, d128  51 /  37 /  41 /  54    32 x 1000, d128  34 / 24.5 / 27 / 37
-//           20 x 3000, d64  105 / 103 / 110 / 132    12 x 512, d64    15 / 10.0 / 8.9 / 7.8
-//   causal  32 x 8192, d128 454 / 496 / 496          29 x 7104, d128 349 / 425 / 616
-//           15 x 6240, d128 185 / 181 / 223          16 x 2048, d128  49 / 34.5 / 34.5
-//           8 x 8192, d64   146 / 122 / 120          11 x 728, d128   24 / 15.3 / 13.2
 hipError_t launch_softmax_pv_deferred(const void* S, const void* V, int64_t BH, int64_t Lq, int64_t Lk, int64_t d,
                                       int causal, void* out, hipStream_t s) {
-    const int64_t n256 = BH * ((Lq + 255) / 256), n128 = BH * ((Lq + 127) / 128);
-    enum { k256, k128, k64, kSplit } layout;
-    if (causal)
-        layout = n256 > 512 ? k256 : n256 > 160 ? k128 : k64;
-    else if (n128 > 256)
-        layout = k256;
-    else if (n128 > 160)
-        layout = k128;
-    else
-        layout = Lk > 64 && Lk <= 1024 ? kSplit : k64;
 #define DN_SOFTMAX_LAYOUT(...)                                                              \
     (d == 64 ? run_softmax_pv<64, __VA_ARGS__>(S, V, BH, Lq, Lk, causal, out, s)            \
              : run_softmax_pv<128, __VA_ARGS__>(S, V, BH, Lq, Lk, causal, out, s))
-    switch (layout) {
-        case k256: return DN_SOFTMAX_LAYOUT(8, 2, 2, 2);
-        case k128: return DN_SOFTMAX_LAYOUT(8, 1, 2, 2);
-        case k64: return DN_SOFTMAX_LAYOUT(4, 1, 2, 2);
+    switch (softmax_layout(BH, Lq, Lk, causal)) {
+        case SoftmaxLayout::k256: return DN_SOFTMAX_LAYOUT(8, 2, 2, 2);
+        case SoftmaxLayout::k128: return DN_SOFTMAX_LAYOUT(8, 1, 2, 2);
+        case SoftmaxLayout::k64: return DN_SOFTMAX_LAYOUT(4, 1, 2, 2);
         default: return DN_SOFTMAX_LAYOUT(4, 1, 2, 2, 2);
     }
 #undef DN_SOFTMAX_LAYOUT

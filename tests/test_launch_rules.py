@@ -1,0 +1,12 @@
+"""The parity tests' sizes against the launch rules (CPU): each reaches the kernel and layout its
+test names, so that a change of a rule cannot leave a kernel untested."""
+import pytest
+
+from tests import launch_rules as R
+from tests import test_attention_layouts
+
+
+def test_attention_layout_sizes():
+    for bq, shapes in test_attention_layouts.LAYOUTS.items():
+        for H, _, Lq, Lk, d, causal in shapes:
+            assert R.prefill(H, Lq, Lk, d, causal) == bq, (H, Lq, Lk, d, causal)
