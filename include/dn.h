@@ -329,13 +329,16 @@ DN_API dn_status attention_decode_deferred(const void* Q, const void* K, const v
  * serving loops, harnesses that forbid hipMalloc): attention_decode_deferred
  * with no workspace argument.  The key-range partials go to a 12 MiB device
  * array that the library holds on each GPU it runs on until the process ends;
- * no call allocates or frees memory.  Every request attention_decode_deferred
- * accepts fits it (the partials stay below 4.25 MiB at d = 64 and 4.125 MiB
- * at d = 128); a request that would not gives DN_ERR_UNSUPPORTED.  The array
- * keeps the last call's partials, which every call overwrites before it reads
- * them; calls that overlap on one GPU (concurrent streams) share it and race.
- * Arguments, layout, grouped-query use and status codes as
- * attention_decode_deferred; the output is bitwise the same.
+ * no call allocates or frees memory.  Heads that fill the chip by themselves
+ * (256 at d = 128, 512 at d = 64), or at most 128 keys, leave no partials: one
+ * workgroup then reads each head whole and the array is not touched.  Every
+ * request attention_decode_deferred accepts fits it (the partials stay below
+ * 4.25 MiB at d = 64 and 4.125 MiB at d = 128); a request that would not gives
+ * DN_ERR_UNSUPPORTED.  The array keeps the last call's partials, which every
+ * call overwrites before it reads them; calls that leave partials and overlap on one GPU (concurrent streams)
+ * share it and race.  Arguments, layout, grouped-query use and status codes as
+ * attention_decode_deferred; the output is bitwise the same as with a workspace
+ * of attention_decode_workspace_bytes.
  */
 DN_API dn_status attention_decode_deferred_noalloc(const void* Q, const void* K, const void* V, int64_t BH,
                                             int64_t Lq, int64_t Lk, int64_t d, float scale, int dtype,

@@ -73,6 +73,17 @@ __device__ __forceinline__ int v_swz(int r) {
     if constexpr (D == 128) return 2 * (r & 3) + 8 * ((r >> 2) & 1);
     return 4 * ((r >> 1) & 1) + 2 * ((r >> 2) & 1);
 }
+// Merging partial sums: 2^(m - mn), and w l rounded by itself (not contracted into the addition
+// that follows).  Partials whose scores are all -inf (m = -inf) weigh nothing, also while the
+// maximum mn of those seen is still -inf.
+__device__ __forceinline__ float part_weight(float m, float mn) {
+    return m != -__builtin_inff() ? __builtin_amdgcn_exp2f(m - mn) : 0.f;
+}
+__device__ __forceinline__ float weighted(float w, float l) {
+    float t = w * l;
+    asm volatile("" : "+v"(t));
+    return t;
+}
 typedef short v4s_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint2 lds_tr16(const char* p) {
     v4s_t r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((DN_LDS v4s_t*)(DN_LDS char*)p);
@@ -574,7 +585,10 @@ struct DecodeArgs {
         return nsplit ? nsplit : (int)((((int64_t)h + 1) * units - 1) / per) - f + 1;
     }
 };
-template <int D>
+// ONE_PASS: a workgroup per head and no partials in memory -- where the deal cuts a head in two
+// (heads enough to fill the chip are cut no further), the workgroup takes both runs and combines
+// their sums in registers, in the merge kernel's arithmetic, so the output is the same bit for bit.
+template <int D, bool ONE_PASS>
 __global__ __launch_bounds__(256) void attention_kernel(const __bf16* __restrict__ Q,
                                                                const __bf16* __restrict__ K,
                                                                const __bf16* __restrict__ V, DecodeArgs p,
@@ -592,8 +606,12 @@ __global__ __launch_bounds__(256) void attention_kernel(const __bf16* __restrict
     const int G = lane >> 4, i = lane & 15;
     const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
     const int64_t total = p.BH * p.units;
-    int64_t pos = p.nsplit ? (int64_t)(wg / p.nsplit) * p.units + (int64_t)(wg % p.nsplit) * p.per : (int64_t)wg * p.per;
-    const int64_t end = p.nsplit ? min((int64_t)(wg / p.nsplit + 1) * p.units, pos + p.per) : min(total, pos + p.per);
+    int64_t pos = ONE_PASS   ? (int64_t)wg * p.units
+                  : p.nsplit ? (int64_t)(wg / p.nsplit) * p.units + (int64_t)(wg % p.nsplit) * p.per
+                             : (int64_t)wg * p.per;
+    const int64_t end = ONE_PASS   ? pos + p.units
+                        : p.nsplit ? min((int64_t)(wg / p.nsplit + 1) * p.units, pos + p.per)
+                                   : min(total, pos + p.per);
 
     // copies: instruction j covers rows RPI j .. of the tile, piece (l % PPR) ^ swz(row)
     const int c_row = lane / PPR;
@@ -614,10 +632,13 @@ __global__ __launch_bounds__(256) void attention_kernel(const __bf16* __restrict
 #pragma unroll
     for (int b = 0; b < DB; ++b) v_off[b] = vr * ROW + (i & 3) * 8 + 32 * (b ^ (v_swz<D>(vr) >> 1));
     const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+    f32x4 v1[DB / 4];  // ONE_PASS: the sums of a cut head's first run
+    float m1 = 0.f, l1 = 0.f;
 
     while (pos < end) {
         const int h = (int)(pos / p.units), u0 = (int)(pos - (int64_t)h * p.units);
-        const int u1 = (int)min((int64_t)p.units, u0 + (end - pos));  // this run's units of head h
+        int u1 = (int)min((int64_t)p.units, u0 + (end - pos));  // this run's units of head h
+        if constexpr (ONE_PASS) u1 = (int)min((int64_t)u1, u0 + (p.per - pos % p.per));
         pos += u1 - u0;
         const uint64_t k_base = uniform_u64(K + (int64_t)h * p.Lk * D), v_base = uniform_u64(V + (int64_t)h * p.Lk * D);
         // the wave's 32 keys of unit u; steps wholly past Lk are none of its work
@@ -730,6 +751,13 @@ __global__ __launch_bounds__(256) void attention_kernel(const __bf16* __restrict
         const bool whole = u0 == 0 && u1 == p.units;
         const int f = p.first_wg(h);
         float* prow = part + ((p.first_slot(h, f) + (p.nsplit ? u0 / p.per : wg - f)) * p.Lq + i) * PR;
+        float a1 = 0.f, a2 = 0.f;  // ONE_PASS, a cut head's second run: weights of the first and of this one
+        if (ONE_PASS && u0 > 0) {
+            const float mn = __builtin_fmaxf(m1, m);
+            a1 = part_weight(m1, mn);
+            a2 = part_weight(m, mn);
+            l = weighted(a1, l1) + weighted(a2, l);
+        }
 #pragma unroll
         for (int bb = 0; bb < DB / 4; ++bb) {
             const int b = wave + 4 * bb;
@@ -740,19 +768,28 @@ __global__ __launch_bounds__(256) void attention_kernel(const __bf16* __restrict
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(wt[w], x[e], v[e]);
             }
+            if constexpr (ONE_PASS) {
+                if (u0 > 0)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(a2, v[e], __builtin_fmaf(a1, v1[bb][e], 0.f));
+                else
+                    v1[bb] = v;
+            }
             if (i < p.Lq) {
-                if (whole) {  // the single deferred division, one rounding to bf16
+                if (whole || (ONE_PASS && u0 > 0)) {  // the single deferred division, one rounding to bf16
                     const float inv = 1.0f / l;
                     uint2 o;
                     o.x = pack_bf16(v[0] * inv, v[1] * inv);
                     o.y = pack_bf16(v[2] * inv, v[3] * inv);
                     *reinterpret_cast<uint2*>(out + ((int64_t)h * p.Lq + i) * D + b * 16 + 4 * G) = o;
-                } else {
+                } else if constexpr (!ONE_PASS) {
                     *reinterpret_cast<f32x4*>(prow + b * 16 + 4 * G) = v;
                 }
             }
         }
-        if (!whole && wave == 0 && G == 0 && i < p.Lq) {
+        m1 = m;
+        l1 = l;
+        if (!ONE_PASS && !whole && wave == 0 && G == 0 && i < p.Lq) {
             prow[D] = l;
             prow[D + 1] = m;
         }
@@ -765,6 +802,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const __bf16* __restrict
 template <int D>
 __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ part, DecodeArgs p,
                                                               __bf16* __restrict__ out) {
+    using namespace fa;
     constexpr int PR = D + 4, PER = D / 64;
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -784,10 +822,9 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) mn = __builtin_fmaxf(mn, __shfl_xor(mn, o));
         mn = __builtin_fmaxf(m, mn);
-        // partials whose scores are all -inf (m = -inf) weigh nothing, also while mn is -inf still
-        const float w = lane < ng && mg != -__builtin_inff() ? __builtin_amdgcn_exp2f(mg - mn) : 0.f;
-        const float old = m != -__builtin_inff() ? __builtin_amdgcn_exp2f(m - mn) : 0.f;
-        l = __builtin_fmaf(l, old, wave_sum(w * lg));
+        const float w = lane < ng ? part_weight(mg, mn) : 0.f;
+        const float old = part_weight(m, mn);
+        l = __builtin_fmaf(l, old, wave_sum(weighted(w, lg)));
         m = mn;
 #pragma unroll
         for (int j = 0; j < PER; ++j) acc[j] *= old;
@@ -814,9 +851,13 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 template <int D>
 static hipError_t run_decode(const void* Q, const void* K, const void* V, const DecodeArgs& a, int64_t wgs, bool split,
                              void* part, void* out, hipStream_t s) {
-    attention_kernel<D><<<dim3((unsigned)wgs), 256, 0, s>>>((const __bf16*)Q, (const __bf16*)K, (const __bf16*)V, a,
-                                                           (float*)part, (__bf16*)out);
-    if (split)
+    if (part)
+        attention_kernel<D, false><<<dim3((unsigned)wgs), 256, 0, s>>>((const __bf16*)Q, (const __bf16*)K,
+                                                                       (const __bf16*)V, a, (float*)part, (__bf16*)out);
+    else
+        attention_kernel<D, true><<<dim3((unsigned)a.BH), 256, 0, s>>>((const __bf16*)Q, (const __bf16*)K,
+                                                                       (const __bf16*)V, a, nullptr, (__bf16*)out);
+    if (part && split)
         attention_merge_kernel<D><<<dim3((unsigned)((a.BH * a.Lq + 3) / 4)), 256, 0, s>>>((const float*)part, a,
                                                                                           (__bf16*)out);
     return hipGetLastError();
@@ -874,17 +915,13 @@ static hipError_t decode_scratch_address(void** out) {
     return hipSuccess;
 }
 
-size_t attention_decode_partials_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d) {
-    int64_t per;
-    const int64_t n = decode_uniform(BH, Lk, d, &per);
-    return n == 1 ? 0 : slots_bytes(BH * n, Lq, d);
-}
-
 hipError_t launch_attention_decode_noalloc(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq,
                                            int64_t Lk, int64_t d, float scale, void* out, hipStream_t s) {
     void* part = nullptr;
-    const hipError_t e = decode_scratch_address(&part);
-    if (e != hipSuccess) return e;
+    if (attention_decode_partials_bytes(BH, Lq, Lk, d) > 0) {
+        const hipError_t e = decode_scratch_address(&part);
+        if (e != hipSuccess) return e;
+    }
     return launch_attention_decode(Q, K, V, BH, Lq, Lk, d, scale, part, kDecodeScratchBytes, out, s);
 }
 

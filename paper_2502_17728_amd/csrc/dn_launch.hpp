@@ -91,17 +91,16 @@ hipError_t launch_attention_deferred(const void* Q, const void* K, const void* V
 
 // Decode attention (Lq <= 16, all Lk keys visible): the keys of all heads dealt evenly to one
 // resident round of workgroups; a head read by several leaves partials in `workspace` that a
-// merge kernel combines.  attention_decode_workspace_bytes of workspace give the even deal;
-// from attention_decode_least_bytes on every head is cut into equally many runs instead.
+// merge kernel combines.  attention_decode_workspace_bytes of workspace give that deal; from
+// attention_decode_least_bytes on every head is cut into equally many runs instead; without a
+// workspace (null) every head is taken whole by one workgroup.
 hipError_t launch_attention_decode(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq, int64_t Lk,
                                    int64_t d, float scale, void* workspace, size_t workspace_bytes, void* out,
                                    hipStream_t s);
 
-// The same with the partials in a library-owned device array of kDecodeScratchBytes per GPU
-// (no workspace argument, no allocation).  attention_decode_partials_bytes: the bytes of
-// partials a call uses there (0 when the heads alone fill the chip and one pass suffices).
+// The same with the partials, where a call leaves any (attention_decode_partials_bytes), in a
+// library-owned device array of kDecodeScratchBytes per GPU (no workspace argument, no allocation).
 constexpr size_t kDecodeScratchBytes = size_t(12) << 20;
-size_t attention_decode_partials_bytes(int64_t BH, int64_t Lq, int64_t Lk, int64_t d);
 hipError_t launch_attention_decode_noalloc(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq,
                                            int64_t Lk, int64_t d, float scale, void* out, hipStream_t s);
 

@@ -35,6 +35,9 @@ void decode(int64_t BH, int64_t Lk, int64_t d, int64_t* units_per_wgs_slots) {
     units_per_wgs_slots[2] = p.wgs;
     units_per_wgs_slots[3] = p.slots;
 }
+size_t noalloc_partials(int64_t BH, int64_t Lq, int64_t Lk, int64_t d) {
+    return attention_decode_partials_bytes(BH, Lq, Lk, d);
+}
 }
 """
 PRODUCT = ("decode", "streamed", "tiles128", "tiles256", "two_stage")
@@ -55,6 +58,7 @@ def _lib():
     lib.streamed.argtypes = [i64] * 3 + [i32] * 2 + [ctypes.POINTER(i32)]
     lib.softmax.argtypes = lib.prefill.argtypes = [i64] * 4 + [i32]
     lib.decode.argtypes = [i64] * 3 + [ctypes.POINTER(i64)]
+    lib.noalloc_partials.argtypes, lib.noalloc_partials.restype = [i64] * 4, ctypes.c_size_t
     return lib
 
 
@@ -85,3 +89,8 @@ def decode(BH, Lk, d):
     out = (ctypes.c_int64 * 4)()
     _lib().decode(BH, Lk, d, out)
     return tuple(out)
+
+
+def noalloc_partials(BH, Lq, Lk, d):
+    """Bytes of partials a decode call without a workspace leaves in the library's array."""
+    return _lib().noalloc_partials(BH, Lq, Lk, d)

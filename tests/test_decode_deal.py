@@ -39,6 +39,7 @@ def test_deal(BH, Lq, Lk, d):
     out = ops.attention_decode_deferred(q, k, v, scale=case["scale"], workspace=ws[:n])
     _check(case, out, BH, Lq, d)
     assert (ws[n:] == 0xff).all()
+    assert torch.equal(out, ops.attention_decode_deferred_noalloc(q, k, v, scale=case["scale"]))
     # the least workspace: every head in the same number of ranges
     w, units = (512 if d == 64 else 256), -(-Lk // 128)
     want = max(1, min(units, -(-w // BH)))

@@ -4,12 +4,15 @@ attention_decode_deferred_noalloc keeps the key-range partials in the library's 
 array; its output must equal attention_decode_deferred's bit for bit, on a first call and on a
 second, smaller one that reuses the array (partials left over from the first must not leak in).
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_2502_17728_amd import inputs as I
+from tests import launch_rules as R
 from tests.parity import TOL, cuda, rowwise_rel_err
 
 pytestmark = pytest.mark.gpu
@@ -55,6 +58,45 @@ def test_noalloc_grouped_query_and_single_pass(ops):
     for case in (gqa, wide):
         got, ref = _both(ops, case)
         assert torch.equal(got, ref)
+
+
+# (heads, rows, keys, d): heads enough to fill the chip, cut by the deal between two workgroups or
+# whole; the same just below that number; one 128-key unit
+ONE_PASS = [(256, 2, 1000, 128), (257, 16, 129, 128), (300, 1, 1000, 128), (511, 1, 300, 128), (512, 3, 300, 128),
+            (513, 1, 129, 64), (600, 4, 700, 64), (1100, 1, 200, 64), (200, 1, 100, 128)]
+
+
+@pytest.mark.parametrize("BH,Lq,Lk,d", ONE_PASS)
+def test_noalloc_one_pass(ops, BH, Lq, Lk, d):
+    # bitwise the workspace entry point's output, with no partials: one kernel and no merge
+    assert R.noalloc_partials(BH, Lq, Lk, d) == 0
+    case = I.make_decode_case(BH, Lq, Lk, d, seed=BH)
+    got, ref = _both(ops, case)
+    assert torch.equal(got, ref)
+    q, k, v = cuda(case["Q"]), cuda(case["K"]), cuda(case["V"])
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        ops.attention_decode_deferred_noalloc(q, k, v, scale=case["scale"], out=got)
+    hip = ctypes.CDLL(next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln))
+    n = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    assert n.value == 1
+
+
+def test_noalloc_one_pass_on_two_streams(ops):
+    # calls without partials may overlap
+    cases = [I.make_decode_case(300, 1, 1000, 128, seed=s) for s in (41, 42)]
+    args = [(cuda(c["Q"]), cuda(c["K"]), cuda(c["V"])) for c in cases]
+    refs = [ops.attention_decode_deferred(*a) for a in args]
+    outs = [[torch.empty_like(r) for _ in range(20)] for r in refs]
+    streams = [torch.cuda.Stream() for _ in args]
+    torch.cuda.synchronize()
+    for i in range(20):
+        for s, a, o in zip(streams, args, outs):
+            ops.attention_decode_deferred_noalloc(*a, out=o[i], stream=s)
+    torch.cuda.synchronize()
+    for r, o in zip(refs, outs):
+        assert all(torch.equal(r, t) for t in o)
 
 
 def test_noalloc_largest_partials_fit(ops):
