@@ -170,25 +170,38 @@ inline Product product_kernel(int64_t M, int64_t N, int64_t K, int dtype, bool g
 }
 
 // ------------------------------------------------------------------------- Softmax -> P.V
-// Layouts, all with two V and two S slots (deeper rings measured no faster), by the number of
-// workgroups they give.  8 waves x 2 fragments (256 queries, 96 KiB of LDS at d = 128) read V
-// least and are best once they fill the chip; 8 x 1 (128 queries) and 4 x 1 (64 queries) give
-// 2 and 4 times the workgroups, two and more to a CU; where even those are few and the keys
-// short, 32 queries with the keys split two ways inside the workgroup.  Measured (us, 256 / 128
-// / 64 queries / split):
+// Layouts, by the number of workgroups they give.  8 waves x 2 fragments (256 queries, two V and
+// two S slots like the others, 96 KiB of LDS at d = 128; deeper rings measured no faster) read V
+// least and are best once they fill the chip; 8 x 1 (128 queries) and 4 x 1 (64 queries) give 2 and
+// 4 times the workgroups, two and more to a CU.  Where one step follows another in too few waves,
+// 32 queries: with the keys split two ways inside the workgroup, or (causal rows, and those of one
+// step, which have nothing to split) unsplit on 4-deep (d = 128: 3-deep) rings.
+// Measured (us, 256 / 128 / 64 queries / 32 split; causal the last one 32 unsplit):
 //   full    27 x 5536, d128 443 / 431 / 499 / 583    10 x 4200, d128 127 / 128 / 132 / 158
 //           16 x 2048, d128  51 /  37 /  41 /  54    32 x 1000, d128  34 / 24.5 / 27 / 37
 //           20 x 3000, d64  105 / 103 / 110 / 132    12 x 512, d64    15 / 10.0 / 8.9 / 7.8
 //   causal  32 x 8192, d128 454 / 496 / 496          29 x 7104, d128 349 / 425 / 616
 //           15 x 6240, d128 185 / 181 / 223          16 x 2048, d128  49 / 34.5 / 34.5
 //           8 x 8192, d64   146 / 122 / 120          11 x 728, d128   24 / 15.3 / 13.2
-enum class SoftmaxLayout { k256, k128, k64, kSplit };
-inline SoftmaxLayout softmax_layout(int64_t BH, int64_t Lq, int64_t Lk, int causal) {
-    const int64_t n256 = BH * ((Lq + 255) / 256), n128 = BH * ((Lq + 127) / 128);
-    if (causal) return n256 > 512 ? SoftmaxLayout::k256 : n256 > 160 ? SoftmaxLayout::k128 : SoftmaxLayout::k64;
-    if (n128 > 256) return SoftmaxLayout::k256;
-    if (n128 > 160) return SoftmaxLayout::k128;
-    return Lk > 64 && Lk <= 1024 ? SoftmaxLayout::kSplit : SoftmaxLayout::k64;
+// The split against 64 queries, by its workgroups n32 and the keys (us, d = 64 and d = 128): at
+// most 256 workgroups, 8 heads x 32 queries x 8192 keys 37 / 64 and 46 / 74, 16 x 300 x 3000
+// 17.9 / 27.5 and 21.9 / 31.6, 200 x 32 x 2048 15.0 / 20.2 and 22.3 / 23.2 (128 queries 22.7 and
+// 27.7); more, 8 x 2048 x 2048
+// 17.9 / 20.9 and 24.7 / 23.9, 16 x 1024 x 1024 10.7 / 12.1 and 14.5 / 14.4, 5 x 3000 x 3000
+// 31.2 / 29.4 and 39.5 / 33.6, 100 x 100 x 3000 31.9 / 29.5 and 40.6 / 33.7.
+// 32 queries unsplit against 64, causal (us): d = 64 8 x 2048 18.2 / 19.4, 4 x 1024 10.5 / 11.1,
+// 1 x 64 3.50 / 3.60; d = 128 8 x 2048 27.1 / 23.4, 4 x 1024 15.1 / 13.0.
+enum class SoftmaxLayout { k256, k128, k64, k32, kSplit };
+inline SoftmaxLayout softmax_layout(int64_t BH, int64_t Lq, int64_t Lk, int64_t d, int causal) {
+    const int64_t n256 = BH * ((Lq + 255) / 256), n128 = BH * ((Lq + 127) / 128), n32 = BH * ((Lq + 31) / 32);
+    if (causal) {
+        if (n256 > 160) return n256 > 512 ? SoftmaxLayout::k256 : SoftmaxLayout::k128;
+        return d == 64 ? SoftmaxLayout::k32 : SoftmaxLayout::k64;
+    }
+    if (n32 <= 256 && Lk > 64) return SoftmaxLayout::kSplit;
+    if (n128 > 160) return n128 > 256 ? SoftmaxLayout::k256 : SoftmaxLayout::k128;
+    if (Lk <= 64) return SoftmaxLayout::k32;
+    return Lk <= (d == 64 ? 2048 : 1024) ? SoftmaxLayout::kSplit : SoftmaxLayout::k64;
 }
 
 // ------------------------------------------------------------------------- attention, prefill

@@ -538,10 +538,13 @@ hipError_t launch_softmax_pv_deferred(const void* S, const void* V, int64_t BH, 
 #define DN_SOFTMAX_LAYOUT(...)                                                              \
     (d == 64 ? run_softmax_pv<64, __VA_ARGS__>(S, V, BH, Lq, Lk, causal, out, s)            \
              : run_softmax_pv<128, __VA_ARGS__>(S, V, BH, Lq, Lk, causal, out, s))
-    switch (softmax_layout(BH, Lq, Lk, causal)) {
+    switch (softmax_layout(BH, Lq, Lk, d, causal)) {
         case SoftmaxLayout::k256: return DN_SOFTMAX_LAYOUT(8, 2, 2, 2);
         case SoftmaxLayout::k128: return DN_SOFTMAX_LAYOUT(8, 1, 2, 2);
         case SoftmaxLayout::k64: return DN_SOFTMAX_LAYOUT(4, 1, 2, 2);
+        case SoftmaxLayout::k32:
+            if (d == 64) return run_softmax_pv<64, 2, 1, 4, 4>(S, V, BH, Lq, Lk, causal, out, s);
+            return run_softmax_pv<128, 2, 1, 3, 3>(S, V, BH, Lq, Lk, causal, out, s);
         default: return DN_SOFTMAX_LAYOUT(4, 1, 2, 2, 2);
     }
 #undef DN_SOFTMAX_LAYOUT

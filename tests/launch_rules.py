@@ -24,7 +24,7 @@ void streamed(int64_t M, int64_t K, int64_t N, int dtype, int gated, int* rf_nc)
     rf_nc[0] = p.rf;
     rf_nc[1] = p.nc;
 }
-int softmax(int64_t BH, int64_t Lq, int64_t Lk, int64_t d, int causal) { return (int)softmax_layout(BH, Lq, Lk, causal); }
+int softmax(int64_t BH, int64_t Lq, int64_t Lk, int64_t d, int causal) { return (int)softmax_layout(BH, Lq, Lk, d, causal); }
 int prefill(int64_t BH, int64_t Lq, int64_t Lk, int64_t d, int causal) {
     return kPrefillBQ[prefill_layout(BH, Lq, Lk, d, causal)];
 }
@@ -41,7 +41,7 @@ size_t noalloc_partials(int64_t BH, int64_t Lq, int64_t Lk, int64_t d) {
 }
 """
 PRODUCT = ("decode", "streamed", "tiles128", "tiles256", "two_stage")
-SOFTMAX = ("256", "128", "64", "split")
+SOFTMAX = ("256", "128", "64", "32", "split")
 F32, BF16 = 0, 1
 
 

@@ -3,10 +3,19 @@ test names, so that a change of a rule cannot leave a kernel untested."""
 import pytest
 
 from tests import launch_rules as R
-from tests import test_attention_layouts
+from tests import test_attention_layouts, test_softmax_layouts
 
 
 def test_attention_layout_sizes():
     for bq, shapes in test_attention_layouts.LAYOUTS.items():
         for H, _, Lq, Lk, d, causal in shapes:
             assert R.prefill(H, Lq, Lk, d, causal) == bq, (H, Lq, Lk, d, causal)
+
+
+def test_softmax_layout_sizes():
+    for name, shapes in test_softmax_layouts.LAYOUTS.items():
+        for BH, L, d, causal in shapes:
+            assert R.softmax(BH, L, L, d, causal) == name, (BH, L, d, causal)
+    for name, shapes in test_softmax_layouts.RAGGED.items():
+        for BH, Lq, Lk, d in shapes:
+            assert R.softmax(BH, Lq, Lk, d, False) == name, (BH, Lq, Lk, d)
