@@ -99,8 +99,9 @@ __device__ __forceinline__ uint2 lds_tr16(const char* p) {
 // maximum, numerators, rare rescale: VALU) and a matrix phase (the products of this step
 // and the scores of the next: MFMA and LDS reads); the two halves of the workgroup run one
 // phase apart, separated by barriers, so that on every SIMD one wave's exponentials run
-// beside the other's matrix instructions.
-template <int D, int NQW, int QW, int KSP, int BKV>
+// beside the other's matrix instructions.  With few key steps (prefill_phased) the phases' start
+// and end cost more than they hide, and the halves run in step (PHASED false).
+template <int D, int NQW, int QW, int KSP, int BKV, bool PHASED>
 __global__ __launch_bounds__(NQW* KSP * 64) void attention_prefill_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V, int64_t Lq, int64_t Lk,
     int causal, float sl2, int nqb, __bf16* __restrict__ out, int group) {
@@ -120,6 +121,7 @@ __global__ __launch_bounds__(NQW* KSP * 64) void attention_prefill_kernel(
     constexpr int DB = D / 16, DC = D / 32;
     static_assert(TILE % (kChunkBytes * CW) == 0 && KSP % NG == 0, "copies split evenly over the late waves");
     static_assert(NW % 2 == 0, "two halves");
+    static_assert(PHASED || KSP == 1, "in step: nothing follows the last step's reads");
     constexpr int XCH = (KSP - 1) * NQW * 64 * QW * (DB + 1) * 16;  // merge exchange
     constexpr int SMEM = KSP * RING > XCH ? KSP * RING : XCH;
 
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(NQW* KSP * 64) void attention_prefill_kernel(
     };
     if (late) {
         issue(0, 0);
-        issue(0, 1);
+        if (PHASED && nsteps > 1) issue(0, 1);
         issue(1, 0);
     }
 
@@ -432,45 +434,63 @@ __global__ __launch_bounds__(NQW* KSP * 64) void attention_prefill_kernel(
     // in phase 2s + 1, the late half one phase later.  K(s+1) and V(s) are read in phases
     // 2s + 1 and 2s + 2; their slots take K(s+3) and V(s+2), issued in phase 2s + 3 and
     // waited for (each wave its own copies) before the barrier that ends phase 2s + 4.
-    wait_vmcnt_asm<0>();
-    block_barrier();
-    if (late) block_barrier();
+    // In step (not PHASED): K(s+1) and V(s+1) land beside step s, in the slots step s - 1 left.
     using yes = std::true_type;
     using no = std::false_type;
-    if (n_w > 0) matrix(-1, no{}, yes{});
-    wait_lgkm0();
-    block_barrier();
-    auto step = [&](int s, auto work, auto next) __attribute__((always_inline)) {  // work: the wave's own step; next: not its last
-        if (late) {
-            issue(0, s + 2);
-            issue(1, s + 1);
-        }
-        if constexpr (decltype(work)::value) {
-            numerators(s);
-            // used here, so that the exponentials are not sunk past the barrier
-#pragma unroll
-            for (int f = 0; f < QW; ++f)
-#pragma unroll
-                for (int kc = 0; kc < NKC; ++kc) asm volatile("" : "+v"(pf[f][kc]));
-        }
+    if constexpr (PHASED) {
+        wait_vmcnt_asm<0>();
         block_barrier();
-        if constexpr (decltype(work)::value) {
-            __builtin_amdgcn_s_setprio(1);
-            matrix(s, yes{}, next);
-            __builtin_amdgcn_s_setprio(0);
-        }
-        if (late) wait_vmcnt_asm<0>();
+        if (late) block_barrier();
+        if (n_w > 0) matrix(-1, no{}, yes{});
         wait_lgkm0();
         block_barrier();
-    };
-    int s = 0;
-    for (; s < n_w - 1; ++s) step(s, yes{}, yes{});
-    if (s < n_w) {
-        step(s, yes{}, no{});
-        ++s;
+        auto step = [&](int s, auto work, auto next) __attribute__((always_inline)) {  // work: the wave's own step; next: not its last
+            if (late) {  // nothing past the last step (tested past the loop: inside, K of one step more costs less)
+                if (decltype(next)::value || s + 2 < nsteps) issue(0, s + 2);
+                if (decltype(next)::value || s + 1 < nsteps) issue(1, s + 1);
+            }
+            if constexpr (decltype(work)::value) {
+                numerators(s);
+                // used here, so that the exponentials are not sunk past the barrier
+#pragma unroll
+                for (int f = 0; f < QW; ++f)
+#pragma unroll
+                    for (int kc = 0; kc < NKC; ++kc) asm volatile("" : "+v"(pf[f][kc]));
+            }
+            block_barrier();
+            if constexpr (decltype(work)::value) {
+                __builtin_amdgcn_s_setprio(1);
+                matrix(s, yes{}, next);
+                __builtin_amdgcn_s_setprio(0);
+            }
+            if (late) wait_vmcnt_asm<0>();
+            wait_lgkm0();
+            block_barrier();
+        };
+        int s = 0;
+        for (; s < n_w - 1; ++s) step(s, yes{}, yes{});
+        if (s < n_w) {
+            step(s, yes{}, no{});
+            ++s;
+        }
+        for (; s < nsteps; ++s) step(s, no{}, no{});
+        if (!late) block_barrier();
+    } else {
+        for (int s = 0; s < nsteps; ++s) {
+            wait_vmcnt_asm<0>();  // this wave's copies of step s have landed
+            wait_lgkm0();         // its reads of step s - 1, whose slots the next copies take, are done
+            block_barrier();      // ... and every wave's
+            if (late && s + 1 < nsteps) {
+                issue(0, s + 1);
+                issue(1, s + 1);
+            }
+            if (s < n_w) {
+                matrix(s - 1, no{}, yes{});
+                numerators(s);
+                matrix(s, yes{}, no{});
+            }
+        }
     }
-    for (; s < nsteps; ++s) step(s, no{}, no{});
-    if (!late) block_barrier();
     wait_vmcnt_asm<0>();  // no copy into LDS may outlive the workgroup
 
     if constexpr (KSP > 1) {
@@ -536,12 +556,12 @@ __global__ __launch_bounds__(NQW* KSP * 64) void attention_prefill_kernel(
     }
 }
 
-template <int D, int NQW, int QW, int KSP, int BKV>
+template <int D, int NQW, int QW, int KSP, int BKV, bool PHASED = true>
 static hipError_t run_attention(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq, int64_t Lk,
                                 int causal, float scale, void* out, hipStream_t s, int group) {
     constexpr int BQ = NQW * QW * 16;
     const int nqb = (int)((Lq + BQ - 1) / BQ);
-    attention_prefill_kernel<D, NQW, QW, KSP, BKV><<<dim3((unsigned)(BH * nqb)), NQW * KSP * 64, 0, s>>>(
+    attention_prefill_kernel<D, NQW, QW, KSP, BKV, PHASED><<<dim3((unsigned)(BH * nqb)), NQW * KSP * 64, 0, s>>>(
         (const __bf16*)Q, (const __bf16*)K, (const __bf16*)V, Lq, Lk, causal, scale * fa::kLog2e, nqb,
         (__bf16*)out, group);
     return hipGetLastError();
@@ -929,7 +949,9 @@ template <int D>
 static hipError_t run_prefill(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq, int64_t Lk,
                               int causal, float scale, void* out, hipStream_t s, int group) {
     switch (prefill_layout(BH, Lq, Lk, D, causal)) {
-        case 0: return run_attention<D, 8, 2, 1, 128>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
+        case 0:
+            if (prefill_phased(Lk)) return run_attention<D, 8, 2, 1, 128>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
+            return run_attention<D, 8, 2, 1, 128, false>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
         case 1: return run_attention<D, 4, 2, 2, 64>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
         case 2: return run_attention<D, 2, 2, 4, 32>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);
         default: return run_attention<D, 2, 1, 4, 32>(Q, K, V, BH, Lq, Lk, causal, scale, out, s, group);

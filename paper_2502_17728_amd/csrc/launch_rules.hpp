@@ -241,6 +241,13 @@ inline int prefill_layout(int64_t BH, int64_t Lq, int64_t Lk, int64_t d, int cau
     return best;
 }
 
+// 256 queries per workgroup: the two halves of a workgroup one phase apart, or in step.  In step /
+// apart (graph replays, us): d = 128 32 heads x 4096 queries x 64 keys 24.5 / 28.0, 1024 65.3 / 66.5,
+// 3000 167.2 / 167.4, 4096 210.8 / 209.4, 8192 806 / 793; causal 512 x 200 28.1 / 34.2, 100 x 700
+// 30.2 / 35.5, 64 x 2048 68.3 / 71.0, 32 x 8192 429.2 / 429.4; d = 64 32 x 4096 x 64 13.8 / 17.0,
+// 2048 70.8 / 71.0, 4096 133.2 / 132.5, 8192 503 / 496.
+inline bool prefill_phased(int64_t Lk) { return Lk > 3072; }
+
 // ------------------------------------------------------------------------- attention, decode
 // Workgroups of one resident round: 128 KiB of LDS at d = 128 (1 per CU), 64 KiB at d = 64 (2).
 inline int64_t decode_resident(int64_t d) { return d == 64 ? 512 : 256; }

@@ -28,6 +28,7 @@ int softmax(int64_t BH, int64_t Lq, int64_t Lk, int64_t d, int causal) { return 
 int prefill(int64_t BH, int64_t Lq, int64_t Lk, int64_t d, int causal) {
     return kPrefillBQ[prefill_layout(BH, Lq, Lk, d, causal)];
 }
+int phased(int64_t Lk) { return prefill_phased(Lk); }
 void decode(int64_t BH, int64_t Lk, int64_t d, int64_t* units_per_wgs_slots) {
     const DecodePlan p = decode_plan(BH, Lk, d);
     units_per_wgs_slots[0] = p.units;
@@ -57,6 +58,7 @@ def _lib():
     lib.narrow.argtypes = [i64] * 2 + [i32] * 2
     lib.streamed.argtypes = [i64] * 3 + [i32] * 2 + [ctypes.POINTER(i32)]
     lib.softmax.argtypes = lib.prefill.argtypes = [i64] * 4 + [i32]
+    lib.phased.argtypes = [i64]
     lib.decode.argtypes = [i64] * 3 + [ctypes.POINTER(i64)]
     lib.noalloc_partials.argtypes, lib.noalloc_partials.restype = [i64] * 4, ctypes.c_size_t
     return lib
@@ -82,6 +84,11 @@ def softmax(BH, Lq, Lk, d, causal):
 def prefill(BH, Lq, Lk, d, causal):
     """Query rows per workgroup."""
     return _lib().prefill(BH, Lq, Lk, d, causal)
+
+
+def phased(Lk):
+    """256 query rows per workgroup: its halves run one phase apart."""
+    return bool(_lib().phased(Lk))
 
 
 def decode(BH, Lk, d):

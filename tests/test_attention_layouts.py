@@ -19,7 +19,11 @@ pytestmark = pytest.mark.gpu
 # (query heads, group, Lq, Lk, d, causal), by the layout the launcher's estimate picks
 LAYOUTS = {
     256: [(96, 1, 513, 513, 128, True), (64, 4, 1025, 700, 128, False), (130, 1, 600, 600, 64, True),
-          (120, 8, 1025, 129, 64, False)],
+          (120, 8, 1025, 129, 64, False), (260, 4, 250, 8, 128, False), (300, 1, 200, 200, 64, True),
+          (100, 4, 700, 700, 128, True), (140, 1, 257, 384, 128, False),
+          # the halves of a workgroup in step up to 3072 keys, one phase apart past that
+          (128, 4, 511, 3072, 128, False), (128, 4, 511, 3073, 128, False), (160, 1, 511, 3200, 64, False),
+          (128, 8, 500, 4999, 64, False)],
     128: [(48, 4, 520, 520, 128, True), (80, 1, 257, 640, 128, False), (64, 2, 520, 520, 64, True)],
     64: [(40, 1, 385, 300, 128, False), (96, 4, 385, 385, 64, True), (40, 1, 520, 1300, 64, False)],
     32: [(24, 8, 449, 449, 128, True), (16, 1, 193, 1500, 128, False), (3, 1, 40, 161, 128, False),

@@ -10,6 +10,9 @@ def test_attention_layout_sizes():
     for bq, shapes in test_attention_layouts.LAYOUTS.items():
         for H, _, Lq, Lk, d, causal in shapes:
             assert R.prefill(H, Lq, Lk, d, causal) == bq, (H, Lq, Lk, d, causal)
+    phased = [(s, R.phased(s[3])) for s in test_attention_layouts.LAYOUTS[256]]
+    for d in (64, 128):  # both schedules of the 256-query layout
+        assert {p for s, p in phased if s[4] == d} == {True, False}
 
 
 def test_softmax_layout_sizes():
