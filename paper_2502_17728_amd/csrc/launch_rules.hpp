@@ -138,7 +138,14 @@ inline void plan_f32(int64_t M, int64_t K, int64_t nblocks, bool gated, int* rf_
 // 200 rows 4096 -> 12288 43 / 63, 313 and 500 rows 4096 -> 6144 35 / 58 and 40 / 59, 300 rows
 // 768 -> 3072 9 / 17; at 1000 rows 4096 -> 12288 it would take 151 against 105.
 // The 0.85 covers the error of the two estimates: at 0.95, 5233 rows of 752 -> 1176 came here
-// and took 28.9 us instead of 27.2.
+// and took 28.9 us instead of 27.2.  The plain product's tiles carry no moments and take about
+// 0.7 of their estimate (streamed / tiles, us: 4096 rows 768 -> 768 13.7 / 10.0, 1500 rows
+// 768 -> 2304 11.3 / 10.7, 512 rows 768 -> 2304 8.4 / 9.6).
+// Past the 4 MiB of an XCD's L2 the row blocks' reads of x cost about 0.7 us per MB more than the
+// plan's estimate (streamed / tiles, eager us: 4096 rows 768 -> 768 15.5 / 14.7, 5500 rows
+// 752 -> 1176 29.2 / 27.3, gated 3100 rows 752 -> 1176 26.4 / 24.6; 3300 rows 768 -> 768
+// 14.5 / 16.8, 3000 rows 1024 -> 1024 16.7 / 19.2).  128 x 128 tiles with a ragged last row block
+// take about 5 % more than their estimate, the two-stage loop 5 % more alone and 5 % less two to a CU.
 // Tiles, per 64 k: 128 x 128 in one round 0.83 us, 256 x 256 1.3 us (1.6 us with the chip full
 // and its clock down), the two-stage 128 x 128 loop 1.6 us alone and 1.9 us two to a CU.
 inline double tiles_estimate_us(int64_t M, int64_t N, int64_t K, bool grouped) {
@@ -157,7 +164,15 @@ inline bool use_skinny(int64_t M, int64_t N, int64_t K, int64_t nblocks, int dty
     if (K >= (int64_t(1) << 22)) return false;
     if (dtype == 0) return true;
     if (M <= kDecodeRows) return false;
-    return M <= 128 || skinny_estimate_us(M, K, nblocks, gated) < 0.85 * tiles_estimate_us(M, N, K, !plain);
+    if (M <= 128) return true;
+    const double us = skinny_estimate_us(M, K, nblocks, gated), tiles = tiles_estimate_us(M, N, K, !plain);
+    if (us >= (plain ? 0.7 : 0.85) * tiles) return false;
+    const double x_mb = 2e-6 * (double)M * (double)K;
+    const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
+    const double fit = use_mid_tiles(M, N, K)   ? (M % 128 ? 1.05 : 1.0)
+                       : use_big_tiles(M, N, K) ? 1.0
+                                                : (tiles128 > 256 ? 0.95 : 1.05);
+    return plain || x_mb < 4.3 || us + 0.7 * x_mb < fit * tiles;
 }
 
 // Which kernel takes a product on packed weights (N counts packed columns).

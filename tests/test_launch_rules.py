@@ -22,3 +22,14 @@ def test_softmax_layout_sizes():
     for name, shapes in test_softmax_layouts.RAGGED.items():
         for BH, Lq, Lk, d in shapes:
             assert R.softmax(BH, Lq, Lk, d, False) == name, (BH, Lq, Lk, d)
+
+
+def test_few_row_rule():
+    # calls that the streamed kernel takes and calls that it had slowed, by the measurements beside the rule
+    for M, K, N, plain, name in [(512, 768, 2304, True, "streamed"), (4096, 768, 768, True, "tiles128"),
+                                 (1500, 768, 2304, True, "tiles128"), (1500, 768, 2304, False, "streamed"),
+                                 (4096, 768, 768, False, "tiles128"), (3300, 768, 768, False, "streamed"),
+                                 (3000, 1024, 1024, False, "streamed"), (5500, 752, 1176, False, "two_stage"),
+                                 (3100, 752, 1176, False, "streamed"), (17, 752, 1176, True, "streamed")]:
+        assert R.product(M, K, N, plain=plain) == name, (M, K, N, plain)
+    assert R.product(3100, 752, 1176, gated=True) == "two_stage"
