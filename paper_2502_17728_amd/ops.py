@@ -136,9 +136,15 @@ def _expect(t: Optional[torch.Tensor], name: str, shape=None, dtype=None, device
 _TORCH_DT = {DN_F32: torch.float32, DN_BF16: torch.bfloat16}
 
 
+# the current stream's handle without building a Stream object (a private name of torch's)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
-    if stream is None:  # the current device's current stream, without building a Stream object
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None:
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

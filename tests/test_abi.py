@@ -4,6 +4,7 @@ these run without a GPU; every call below fails validation)."""
 import ctypes
 import os
 import re
+import types
 
 import pytest
 
@@ -379,3 +380,9 @@ def test_binding_checks_norm_and_gemm_shapes():
         ops.gemm(_bf(4, 72), _prepared(64, 16))
     with pytest.raises(ValueError, match="B has dtype"):
         ops.gemm(_bf(4, 64), torch.zeros(64, 16))
+
+
+def test_current_stream_without_torchs_private_name(monkeypatch):
+    monkeypatch.setattr(ops, "_raw_stream", None)
+    monkeypatch.setattr(ops.torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert ops._stream(None) == 77 and ops._stream(5) == 5
