@@ -7,7 +7,9 @@ namespace dn {
 template <int NC, Skinny KIND>
 static hipError_t skinny_rf(int rf, const SkinnyArgs& a, hipStream_t s) {
     switch (rf) {
-        case 1: return run_skinny_kernel<float, 1, 8, NC, KIND>(a, s);
+        case 1:
+            if constexpr (NC == 6) return hipErrorInvalidValue;  // not planned: two-deep rings only
+            else return run_skinny_kernel<float, 1, 8, NC, KIND>(a, s);
         case 2: return run_skinny_kernel<float, 2, 4, NC, KIND>(a, s);
         case 4: return run_skinny_kernel<float, 4, 2, NC, KIND>(a, s);
         default: return run_skinny_kernel<float, 8, 1, NC, KIND>(a, s);

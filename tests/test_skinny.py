@@ -1,7 +1,8 @@
-"""The streamed few-row kernel (17 rows and up, bf16) at the sizes where it can go wrong: every
-row-block height and its remainders, more than one row block, K that ends inside a 32- or
-64-k chunk or within the first stage, ragged column blocks; LayerNorm, RMSNorm, gated and
-plain.  Rows of guard values around the output must survive.
+"""The streamed kernel (bf16 from 17 rows, fp32 of any) at small sizes where it can go wrong: row
+counts around its row blocks, more than one row block, K that ends inside a 32- or 64-k chunk or
+within the first stage, ragged column blocks; LayerNorm, RMSNorm, gated and plain.  Small outputs
+take its smaller variants (every variant: test_skinny_plans).  Rows of guard values around the
+output must survive.
 
 Bounds: the row-normwise bound of the parity tests, and on the 2-norm of the whole error
 4e-3 (gated 6e-3): W' and the output round to bf16 once each, 2^-9 / sqrt(3) rms at most
