@@ -92,9 +92,9 @@ def test_ln_linear_bf16_ragged(ops, M, K, N):
     _ln_check(ops, I.make_ln_case(M, K, N, "bf16", seed=M + K))
 
 
-# token counts on both sides of each decode-layout switch (16 | 17..32 | 33..48 |
-# 49..64 | 65..96 | 97..128 | 129 = the tiled kernels), partial row fragments; K = 8
-# leaves most K-slices empty, N = 24 / 520 leave a partial group of column blocks
+# token counts on both sides of the decode kernel's last row (16) and of the row blocks of the
+# streamed kernel past it, partial row fragments; K = 8 leaves most K-slices empty, N = 24 / 520
+# leave a partial group of column blocks
 @pytest.mark.parametrize("M", [1, 3, 4, 5, 8, 9, 16, 17, 32, 33, 48, 49, 63, 64, 65, 81, 96, 97, 127, 128, 129])
 @pytest.mark.parametrize("K,N", [(1024, 520), (8200, 64), (8, 24)])
 def test_ln_linear_bf16_decode_shapes(ops, M, K, N):
@@ -103,8 +103,7 @@ def test_ln_linear_bf16_decode_shapes(ops, M, K, N):
 
 @pytest.mark.parametrize("M,N", [(100, 20352), (100, 20608), (128, 20352)])
 def test_ln_linear_bf16_batched_decode_switch(ops, M, N):
-    # 65-128 tokens take the streaming kernel below 160 tiles of 128 x 128 (159 here) and
-    # the tiled kernel from 160 tiles (161)
+    # 65-128 tokens over wide outputs (159 and 161 tiles of 128 x 128): the streamed kernel
     _ln_check(ops, I.make_ln_case(M, 256, N, "bf16", seed=N % 97, outliers=2))
 
 
@@ -127,15 +126,15 @@ def test_ln_linear_constant_rows_give_b(ops):
 
 @pytest.mark.parametrize("M,K,N", [(4000, 544, 4104), (4000, 520, 4104), (4096, 4096, 4096)])
 def test_ln_linear_bf16_large_tiles(ops, M, K, N):
-    # >= 256 output tiles of 256x256: the pipelined main loop with ragged M and N (K % 32 == 0);
-    # K = 520 takes the 128x128 loop with its K tail
+    # many rows: the streamed kernel at K = 544 and 520, with its K tail (a size by size view of the
+    # tile kernels: test_tile_kernels), and 256 x 256 tiles at K = 4096
     case = I.make_ln_case(M, K, N, "bf16", seed=M % 97, outliers=3)
     _ln_check(ops, case)
 
 
-# K >= 8192 on the 256x256 loop, one tile per workgroup and the row moments shared between the
-# column groups of each row block: (2100, 8256, 4200) ragged M and N over 9 x 17 tiles,
-# (2048, 8192, 4096) 8 x 16; every 7th row (all 16-row fragments of every row block) against the
+# K >= 8192 on the pipelined 256 x 192 tiles, one tile per workgroup and the row moments shared
+# between the column groups of each row block: (2100, 8256, 4200) ragged M and N over 9 x 22 tiles,
+# (2048, 8192, 4096) 8 x 22; every 7th row (all 16-row fragments of every row block) against the
 # oracle
 @pytest.mark.parametrize("M,K,N,norm", [(2100, 8256, 4200, "layernorm"), (2048, 8192, 4096, "layernorm"),
                                         (2100, 8256, 4200, "rms")])
@@ -147,10 +146,9 @@ def test_norm_linear_bf16_long_k(ops, M, K, N, norm):
 @pytest.mark.parametrize("M,K,N,layout", [(4104, 320, 4096, 2), (4104, 264, 4096, 2), (4104, 264, 4096, 1),
                                            (300, 136, 264, 2), (257, 512, 1032, 2), (2100, 8256, 4200, 2)])
 def test_gemm_large(ops, M, K, N, layout):
-    # layout 2 (packed weights, gamma = 1) with K % 64 == 0 runs the pipelined loop, on
-    # 256 x 256 tiles at 4104 rows and at 2100 x 4200 with K = 8256 (every 7th row checked) and
-    # on 128 x 128 tiles at 257 x 1032 (27 tiles); K = 264 and K = 136 run the two-stage
-    # 128 x 128 loop
+    # layout 2 (packed weights, gamma = 1) with K % 64 == 0 runs the pipelined loop on 256 x 192
+    # tiles at 4104 rows and at 2100 x 4200 with K = 8256 (every 7th row checked), K = 264 the
+    # two-stage 128 x 128 loop (layout 1 too), and the sizes of 300 and 257 rows the streamed kernel
     g = torch.Generator().manual_seed(5)
     A = torch.randn(M, K, generator=g).to(torch.bfloat16)
     B = torch.randn(K, N, generator=g).to(torch.bfloat16)
@@ -205,8 +203,8 @@ def test_ln_linear_ffn_decode_workload(ops, t):
 @pytest.mark.parametrize("t", [32, 128, 1024])
 def test_ln_linear_qkv_tokens_workload_all_rows(ops, t):
     # the QKV projection at the bench's batched-decode and prefill-chunk sizes, in the
-    # launch configurations it times: 2 and 8 row fragments of the streaming kernel, and
-    # 4 x 48 tiles of 256 x 256 (one tile per workgroup, each reducing its rows' moments)
+    # launch configurations it times: the streamed kernel, and 4 x 64 tiles of 256 x 192 (one
+    # tile per workgroup, the row moments shared between them)
     _ln_check_all_rows(ops, I.make_ln(I.ln_qkv_tokens(t)), f"ln_linear_deferred qkv {t} tokens")
 
 
@@ -229,7 +227,8 @@ def test_ln_linear_guard_band(ops):
     assert (buf[:512] == 7.0).all() and (buf[-512:] == 7.0).all()
 
 
-# Shared row moments: on the pipelined kernels the workgroups of a row block each reduce a share
+# Shared row moments (each tile kernel at sizes of its own: test_tile_kernels; of the sizes here the
+# second and third take the streamed kernel, which has no exchange): on the pipelined kernels the workgroups of a row block each reduce a share
 # of its rows' moments and exchange them through a device mailbox, every word stamped with its
 # call's number.  A bound of 0 on the wait for the peers' shares makes every workgroup reduce all
 # its rows itself -- the path taken when a peer is not resident.
@@ -296,8 +295,8 @@ def test_ln_linear_graph_replays_follow_new_inputs(ops):
 # Non-finite inputs propagate as in the plain definition (Eq. (1)-(2), Eq. (6)): a row holding
 # NaN, +inf or -inf gives an all-NaN output row and leaves every other row untouched; with
 # eps = 0 a constant row (LayerNorm: zero variance) or an all-zero row (RMSNorm) gives 0/0 = NaN.
-# The shapes take every kernel: fp32 tiles, the 128 x 128 two-stage loop (K % 64 != 0), the
-# pipelined 128 x 128 and 256 x 256 kernels, and the decode kernel with 1 and 3 row fragments.
+# The shapes take the streamed kernel in fp32 and (three of them) bf16, 256 x 192 tiles and the
+# decode kernel; the other tile kernels: test_tile_kernels.
 NONFINITE_SHAPES = [(37, 104, 72, "f32"), (200, 520, 392, "bf16"), (300, 256, 4104, "bf16"),
                     (520, 256, 8200, "bf16"), (5, 1024, 520, "bf16"), (40, 1024, 520, "bf16")]
 
@@ -413,7 +412,7 @@ def test_ln_linear_norm_on_load_rejects_small_shapes(ops):
 
 
 # (1024, 512, 4096): 128 x 128 pipelined tiles whose workgroups exchange row moments;
-# (4104, 320, 4096): 256 x 256 tiles exchanging them; (100, 1024, 520): 8 decode fragments
+# (4104, 320, 4096): 256 x 192 tiles exchanging them; (257, 1024, 264): the streamed kernel
 @pytest.mark.parametrize("M,K,N,dtype,norm", [(37, 104, 72, "f32", "layernorm"), (257, 1024, 264, "bf16", "layernorm"),
                                               (5, 1024, 520, "bf16", "layernorm"), (50, 1024, 520, "bf16", "layernorm"),
                                               (100, 1024, 520, "bf16", "layernorm"),
@@ -422,8 +421,8 @@ def test_ln_linear_norm_on_load_rejects_small_shapes(ops):
                                               (300, 512, 200, "bf16", "rms"), (3, 8200, 64, "bf16", "rms")])
 def test_linear_deferred_post(ops, M, K, N, dtype, norm):
     # post-LN placement: the deferred product and the normalized rows (the residual branch) from
-    # the statistics the product's kernel reduced; covers the fp32, 128x128, decode and 256x256
-    # kernels, each exporting the statistics once per row
+    # the statistics the product's kernel reduced; the streamed (fp32 and
+    # bf16), decode and tile kernels, each exporting the statistics once per row
     rms = norm == "rms"
     case = I.make_ln_case(M, K, N, dtype, seed=M + K + 7, outliers=2, norm=norm)
     g, b = cuda(case["gamma"]), cuda(case["beta"])
@@ -471,8 +470,8 @@ def test_linear_deferred_post_qkv_workload_statistics(ops):
 
 
 def test_linear_deferred_post_long_k_statistics(ops):
-    # the statistics exported by the 256 x 256 kernel at K = 8192 with the row moments shared
-    # between 16 column groups: every row's (mean, rstd) against the definition, the product on
+    # the statistics exported by the 256 x 192 tiles at K = 8192 with the row moments shared
+    # between 22 column groups: every row's (mean, rstd) against the definition, the product on
     # every 7th row
     M, K, N = 2048, 8192, 4096
     case = I.make_ln_case(M, K, N, "bf16", seed=17, outliers=2)
@@ -564,8 +563,8 @@ def _swiglu_check(ops, case, rows=None):
 
 
 def test_rms_swiglu_graph_replays_follow_new_inputs(ops):
-    # the gated product recorded in a HIP graph (a shape whose direct launches exchange row
-    # moments between workgroups) and replayed on new contents of the same x buffer
+    # the gated product recorded in a HIP graph and replayed on new contents of the same x buffer
+    # (shapes whose direct launches exchange row moments: test_tile_kernels)
     cases = [I.make_swiglu_case(1024, 512, 2048, "bf16", seed=70 + i, outliers=2) for i in range(3)]
     a = cases[0]
     w = ops.swiglu_prepare(cuda(a["Wg"]), cuda(a["Wu"]), cuda(a["gamma"]))
@@ -604,15 +603,15 @@ def test_rms_swiglu_bf16_ragged(ops, M, K, N):
 @pytest.mark.parametrize("M", [1, 8, 9, 16, 17, 33, 48, 49, 63, 64, 65, 96, 97, 128])
 @pytest.mark.parametrize("K,N", [(1024, 520), (8, 24)])
 def test_rms_swiglu_bf16_decode_shapes(ops, M, K, N):
-    # 1-7 gate/up pairs per workgroup, 1-8 row fragments (33, 49 and 63 rows leave the last
-    # fragment partial under the two-pair layout); N = 520 / 24 leave a partial pair group
+    # the decode kernel up to 16 rows, then the streamed kernel with 2 row fragments (its other
+    # variants: test_skinny_plans); N = 520 / 24 leave a partial pair group
     _swiglu_check(ops, I.make_swiglu_case(M, K, N, "bf16", seed=M * 3 + 1, outliers=4))
 
 
 @pytest.mark.parametrize("M,K,N", [(4000, 544, 2056), (4000, 520, 2056), (2100, 8256, 2104)])
 def test_rms_swiglu_bf16_large_tiles(ops, M, K, N):
-    # 2 x 2056 packed columns: 16 x 17 tiles of 256 x 256 (pipelined loop, ragged M and N); K = 520
-    # takes the 128 x 128 loop; K = 8256 runs 129 stages (every 7th row checked)
+    # K = 544 and 520 take the two-stage 128 x 128 loop; K = 8256 runs 129 stages on pipelined
+    # 256 x 192 tiles (every 7th row checked)
     _swiglu_check(ops, I.make_swiglu_case(M, K, N, "bf16", seed=M % 83, outliers=3),
                   rows=np.arange(0, M, 7) if K > 4096 else None)
 
