@@ -296,8 +296,8 @@ DN_API dn_status attention_gqa_deferred(const void* Q, const void* K, const void
 /*
  * Decode-shaped attention: Lq <= 16 query rows per head against all Lk keys
  * (the key/value cache holds exactly the visible keys, so no mask).  The keys
- * of all heads are dealt evenly to one resident round of workgroups; where a
- * head's keys went to several, each leaves its un-normalized partial sums
+ * of all heads are dealt in order to at most one resident round of workgroups,
+ * the same number of 128-key units to each but the last; where a head's keys went to several, each leaves its un-normalized partial sums
  * (acc, l and the reference max m, fp32) in `workspace`, and one merge kernel
  * combines them, m = max m_g, out = sum 2^(m_g - m) acc_g /
  * sum 2^(m_g - m) l_g -- the deferred division of Eq. (8) once more, across

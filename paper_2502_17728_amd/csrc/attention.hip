@@ -29,9 +29,9 @@
 // the diagonal inside a step are masked to -inf before the exponentials.
 //
 // Prefill (attention_prefill_kernel).  Bound by the matrix cores and by the power they and
-// the exponentials draw: causal 32 x 8192, d = 128 runs the pipe 65-68 % busy at 1.6-1.74 GHz
-// (55 % at 2.0 GHz before the two halves of a workgroup ran out of phase), 473 us against
-// 521 us in one run; 4096 keys without a mask 221 us against 239 us.
+// the exponentials draw: causal 32 x 8192, d = 128 runs the pipe 68 % busy at 1.92 GHz (54.6 % at
+// 2.03 GHz before the two halves of a workgroup ran out of phase), 434 us against 507 us in one
+// run; 4096 keys without a mask 215 us against 235 us.
 //
 // Decode (a few new queries against a long key/value cache): attention_kernel below.
 #include <algorithm>
@@ -568,9 +568,10 @@ static hipError_t run_attention(const void* Q, const void* K, const void* V, int
 }
 
 // Decode: up to 16 query rows per head against all keys.  The keys of all heads, in units of
-// 128, are dealt evenly and in order to the workgroups of one resident round, so a workgroup
-// takes a run of units that may end one head and begin the next; whatever the head count and
-// cache length, no workgroup has more than one unit more than another.
+// 128, are dealt in order to at most one resident round of W workgroups, ceil(units / W) to each
+// and the rest to the last, so a workgroup takes a run of units that may end one head and begin
+// the next, and none has more than an even share rounded up.  Where that rounding is coarse,
+// places stay empty: 17 heads x 1992 keys, 272 units, are 136 workgroups of 2 on 256 places.
 //
 // The four waves of a workgroup take 32 keys of each unit and stream them through K/V rings of
 // their own (two slots, no barrier; four waves keep up to 128 KiB in flight, one wave's counter

@@ -89,9 +89,9 @@ hipError_t launch_attention_deferred(const void* Q, const void* K, const void* V
                                      int64_t Lk, int64_t d, int causal, float scale, void* out, hipStream_t s,
                                      int group = 1);
 
-// Decode attention (Lq <= 16, all Lk keys visible): the keys of all heads dealt evenly to one
-// resident round of workgroups; a head read by several leaves partials in `workspace` that a
-// merge kernel combines.  attention_decode_workspace_bytes of workspace give that deal; from
+// Decode attention (Lq <= 16, all Lk keys visible): the keys of all heads dealt in order to at
+// most one resident round of workgroups; a head read by several leaves partials in `workspace`
+// that a merge kernel combines.  attention_decode_workspace_bytes of workspace give that deal; from
 // attention_decode_least_bytes on every head is cut into equally many runs instead; without a
 // workspace (null) every head is taken whole by one workgroup.
 hipError_t launch_attention_decode(const void* Q, const void* K, const void* V, int64_t BH, int64_t Lq, int64_t Lk,

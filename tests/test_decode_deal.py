@@ -1,8 +1,8 @@
 """Decode attention over every way the keys can be dealt: whole heads per workgroup, heads cut
 between two workgroups, heads cut into many, runs that end one head and begin the next, cache
 lengths around the 128-key unit and the 32-key steps, one key, and the smaller workspace that
-cuts every head alike.  2-norm bound as for prefill: 4e-3 (numerators and output round to bf16,
-1.6e-3 rms together)."""
+cuts every head alike; with a workspace and (bitwise the same) without.  2-norm bound as for
+prefill: 4e-3 (numerators and output round to bf16, 1.6e-3 rms together)."""
 import numpy as np
 import pytest
 import torch
