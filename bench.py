@@ -53,60 +53,52 @@ PEAK_HBM_GBS = 8000.0       # HBM3E
 ROUNDS = 7                  # rounds of the alternating isolated timings
 
 # HBM traffic per launch, from two rocprofv3 --pmc runs of this script (FETCH_SIZE, then WRITE_SIZE,
-# KiB per dispatch, averaged over the timed launches), each scaled by what the same counter reads for
+# KiB per dispatch, the median over the launches), each scaled by what the same counter reads for
 # a plain device copy of 1 GiB in the same run (--calib-copy-mib 1024): FETCH_SIZE reads 524306 KiB
 # for its 1048576 KiB (x 1.99993), WRITE_SIZE reads 1048576 KiB (x 1.0).  A figure is only valid for
 # the kernel source it was taken on: each entry carries the sha256 of its kernel's source files, and
 # the bench reports null once they differ.
-KERNEL_SOURCES = {"softmax_pv_deferred": ("softmax_pv.hip", "dn_device.hpp"),
-                  "attention_deferred": ("attention.hip", "dn_device.hpp"),
-                  "attention_decode_deferred": ("attention.hip", "dn_device.hpp"),
-                  "ln_linear_deferred": ("ln_gemm.hip", "dn_device.hpp"),
-                  "rms_linear_deferred": ("ln_gemm.hip", "dn_device.hpp"),
-                  "rms_swiglu_deferred": ("ln_gemm.hip", "dn_device.hpp")}
-TRAFFIC = {
-    ("softmax_pv_deferred", "causal_softmax_pv_bf16_32x8192x8192_d128"): {
-        "sha256": ("1e53f8da44a9052000f4f06cc602aab1e7006d1f2937744eb6cc849bb3ca4a32",
-                   "7aed1bedca8bd2cd6a906eb0bca1de03527ccb5d1d5a9406e8d4b87a37846ee9"),
-        "fetch_kib": 1185486, "fetch_scale": 1.99988, "write_kib": 65771, "write_scale": 1.0},
-    ("softmax_pv_deferred", "softmax_pv_bf16_12x512x512_d64"): {
-        "sha256": ("8348feaf7e161752c3966e3a1e5f5235f20f8403ef203d36c1487a1565ffb446",
-                   "ac9c5fe92ec45f657c9519fcd8d54a4977d6a85897f645cae15b69abf72ca89a"),
-        "fetch_kib": 3676, "fetch_scale": 1.99990, "write_kib": 768, "write_scale": 1.0},
-    ("ln_linear_deferred", "ln_qkv_bf16_4096x4096x12288"): {
-        "sha256": ("70ff13ee8dfa009c3eb542e1df3eb31c525d39718e9311900f3f1a3c58b46307",
-                   "ac9c5fe92ec45f657c9519fcd8d54a4977d6a85897f645cae15b69abf72ca89a"),
-        "fetch_kib": 298905, "fetch_scale": 1.99992, "write_kib": 109686, "write_scale": 1.0},
-    ("ln_linear_deferred", "ln_ffn_up_bf16_8192x8192x28672"): {
-        "sha256": ("70ff13ee8dfa009c3eb542e1df3eb31c525d39718e9311900f3f1a3c58b46307",
-                   "ac9c5fe92ec45f657c9519fcd8d54a4977d6a85897f645cae15b69abf72ca89a"),
-        "fetch_kib": 2768553, "fetch_scale": 1.99993, "write_kib": 481424, "write_scale": 1.0},
-    ("ln_linear_deferred", "ln_ffn_up_bf16_decode_t1_8192x28672"): {
-        "sha256": ("70ff13ee8dfa009c3eb542e1df3eb31c525d39718e9311900f3f1a3c58b46307",
-                   "ac9c5fe92ec45f657c9519fcd8d54a4977d6a85897f645cae15b69abf72ca89a"),
-        "fetch_kib": 233660, "fetch_scale": 1.99986, "write_kib": 56, "write_scale": 1.0},
-    ("ln_linear_deferred", "ln_linear_f32_128x768x3072"): {
-        "sha256": ("70ff13ee8dfa009c3eb542e1df3eb31c525d39718e9311900f3f1a3c58b46307",
-                   "ac9c5fe92ec45f657c9519fcd8d54a4977d6a85897f645cae15b69abf72ca89a"),
-        "fetch_kib": 6296, "fetch_scale": 1.99992, "write_kib": 1536, "write_scale": 1.0},
-    ("rms_linear_deferred", "rms_qkv_bf16_4096x4096x6144"): {
-        "sha256": ("70ff13ee8dfa009c3eb542e1df3eb31c525d39718e9311900f3f1a3c58b46307",
-                   "ac9c5fe92ec45f657c9519fcd8d54a4977d6a85897f645cae15b69abf72ca89a"),
-        "fetch_kib": 164194, "fetch_scale": 1.99993, "write_kib": 52852, "write_scale": 1.0},
-    ("rms_swiglu_deferred", "rms_swiglu_bf16_decode_t1_8192x28672"): {
-        "sha256": ("70ff13ee8dfa009c3eb542e1df3eb31c525d39718e9311900f3f1a3c58b46307",
-                   "ac9c5fe92ec45f657c9519fcd8d54a4977d6a85897f645cae15b69abf72ca89a"),
-        "fetch_kib": 459121, "fetch_scale": 1.99994, "write_kib": 56, "write_scale": 1.0},
-    ("attention_deferred", "causal_attention_bf16_32x8192x8192_d128"): {
-        "sha256": ("14a2cff4eb034e7df2315b259769531806cc5f9dec6aea0e4ffa9e793cd9780b",
-                   "7aed1bedca8bd2cd6a906eb0bca1de03527ccb5d1d5a9406e8d4b87a37846ee9"),
-        "fetch_kib": 247764, "fetch_scale": 1.99991, "write_kib": 65577, "write_scale": 1.0},
-    # 256 heads fill the chip with one workgroup per head: no key split, no merge kernel
-    ("attention_decode_deferred", "decode_attention_bf16_256x1x8192_d128"): {
-        "sha256": ("14a2cff4eb034e7df2315b259769531806cc5f9dec6aea0e4ffa9e793cd9780b",
-                   "7aed1bedca8bd2cd6a906eb0bca1de03527ccb5d1d5a9406e8d4b87a37846ee9"),
-        "fetch_kib": 524414, "fetch_scale": 1.99989, "write_kib": 64, "write_scale": 1.0},
+
+# sources of each entry point's kernels and of the rules that pick among them
+_PRODUCT_SOURCES = ("ln_gemm.hip", "ln_skinny.hpp", "ln_skinny.hip", "ln_skinny_f32.hip", "launch_rules.hpp",
+                    "dn_device.hpp")
+KERNEL_SOURCES = {"softmax_pv_deferred": ("softmax_pv.hip", "launch_rules.hpp", "dn_device.hpp"),
+                  "attention_deferred": ("attention.hip", "launch_rules.hpp", "dn_device.hpp"),
+                  "attention_decode_deferred": ("attention.hip", "launch_rules.hpp", "dn_device.hpp"),
+                  "ln_linear_deferred": _PRODUCT_SOURCES,
+                  "rms_linear_deferred": _PRODUCT_SOURCES,
+                  "rms_swiglu_deferred": _PRODUCT_SOURCES}
+# the sources the figures below were taken on
+_TAKEN_ON = {
+    "attention.hip": "cc332201b0474e996589799bda0cedf1acef0142942522b9ae2675ada6a0229b",
+    "dn_device.hpp": "7aed1bedca8bd2cd6a906eb0bca1de03527ccb5d1d5a9406e8d4b87a37846ee9",
+    "launch_rules.hpp": "23825b93bd12287e2b8b54f71b5f938aa90c0b8e6ca16f7b570de34219bf0299",
+    "ln_gemm.hip": "b6d7c815d1e885c049b828f62852980ed98cbd906791cf46574b6e285c26d36e",
+    "ln_skinny.hip": "4f23350112f84e2f7dc2e0451c02c4d7d0b5dd49472d5d6347d604c0a7352a80",
+    "ln_skinny.hpp": "67814d2f1a9f4db68f053b4c82023a7d9ba8567d6e1105c8d7140bba4f66b953",
+    "ln_skinny_f32.hip": "2c6d30cdd573ce203e4d88ee7a3890a3e4e86c7790a50bde2175c33499f37a81",
+    "softmax_pv.hip": "c80cf89d201c0aa5f72e7e037648078d5c59aded852ef7283b3e1034dbed3320",
 }
+
+
+def _figure(kernel, fetch_kib, fetch_scale, write_kib, write_scale=1.0):
+    return {"sha256": tuple(_TAKEN_ON[f] for f in KERNEL_SOURCES[kernel]), "fetch_kib": fetch_kib,
+            "fetch_scale": fetch_scale, "write_kib": write_kib, "write_scale": write_scale}
+
+
+TRAFFIC = {(kernel, workload): _figure(kernel, *figures) for kernel, workload, *figures in (
+    ("softmax_pv_deferred", "causal_softmax_pv_bf16_32x8192x8192_d128", 1186058, 1.99992, 65748),
+    ("softmax_pv_deferred", "softmax_pv_bf16_12x512x512_d64", 3680, 1.99993, 768),
+    ("ln_linear_deferred", "ln_qkv_bf16_4096x4096x12288", 298954, 1.99994, 109946),
+    ("ln_linear_deferred", "ln_ffn_up_bf16_8192x8192x28672", 2768553, 1.99993, 483157),
+    ("ln_linear_deferred", "ln_ffn_up_bf16_decode_t1_8192x28672", 239504, 1.99994, 56),
+    ("ln_linear_deferred", "ln_linear_f32_128x768x3072", 6230, 1.99993, 1536),
+    ("rms_linear_deferred", "rms_qkv_bf16_4096x4096x6144", 164191, 1.99994, 52479),
+    ("rms_swiglu_deferred", "rms_swiglu_bf16_decode_t1_8192x28672", 459122, 1.99993, 56),
+    ("attention_deferred", "causal_attention_bf16_32x8192x8192_d128", 247838, 1.99992, 65642),
+    # 256 heads fill the chip with one workgroup per head: no key split, no merge kernel
+    ("attention_decode_deferred", "decode_attention_bf16_256x1x8192_d128", 524409, 1.99992, 64),
+)}
 
 
 def measured_traffic(kernel: str, workload: str):
