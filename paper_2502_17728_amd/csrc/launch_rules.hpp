@@ -39,10 +39,11 @@ inline TilePlan plan_tiles(int64_t tm, int64_t tn, bool grouped) {
 // two full rounds instead of 384 square ones in 1.5; 1024 x 4096 -> 12288: 256
 // instead of 192 on 256 CUs.
 constexpr double kNarrowCost = 0.8;
-inline bool use_narrow_tiles(int64_t M, int64_t N, bool grouped) {
+inline TilePlan plan_256_tiles(int64_t M, int64_t N, bool grouped, bool* narrow) {
     const int64_t tm = (M + 255) / 256;
-    return (double)plan_tiles(tm, (N + 191) / 192, grouped).times * kNarrowCost <
-           (double)plan_tiles(tm, (N + 255) / 256, grouped).times;
+    const TilePlan square = plan_tiles(tm, (N + 255) / 256, grouped), thin = plan_tiles(tm, (N + 191) / 192, grouped);
+    *narrow = (double)thin.times * kNarrowCost < (double)square.times;
+    return *narrow ? thin : square;
 }
 
 // The 256x256 kernel past 128 rows (and K a multiple of its stage), where the

@@ -1276,9 +1276,10 @@ static uint32_t moment_wait_ticks() {
 template <Epi EPI, int BT = 256>
 static hipError_t run_pipe(const MainArgs& args, hipStream_t s) {
     MainArgs a = args;
-    const bool narrow = BT == 256 && use_narrow_tiles(a.M, a.N, EPI != Epi::kGemm);
-    const int64_t cols = narrow ? 192 : BT;
-    const TilePlan plan = plan_tiles((a.M + BT - 1) / BT, (a.N + cols - 1) / cols, EPI != Epi::kGemm);
+    constexpr bool kGrouped = EPI != Epi::kGemm;
+    bool narrow = false;
+    const TilePlan plan = BT == 256 ? plan_256_tiles(a.M, a.N, kGrouped, &narrow)
+                                    : plan_tiles((a.M + BT - 1) / BT, (a.N + BT - 1) / BT, kGrouped);
     const int64_t group = plan.group, ngroups = plan.ngroups, wgs = plan.wgs;
     // Shared moments where the workgroups of a row block are co-resident (one round of
     // workgroups: 256 at one per CU, 512 for the 128 x 128 tiles at two per CU) and number

@@ -16,7 +16,11 @@ extern "C" {
 int product(int64_t M, int64_t K, int64_t N, int dtype, int gated, int plain) {
     return (int)product_kernel(M, packed(N, gated), K, dtype, gated, plain);
 }
-int narrow(int64_t M, int64_t N, int gated, int plain) { return use_narrow_tiles(M, packed(N, gated), !plain); }
+int narrow(int64_t M, int64_t N, int gated, int plain) {
+    bool narrow;
+    plan_256_tiles(M, packed(N, gated), !plain, &narrow);
+    return narrow;
+}
 void streamed(int64_t M, int64_t K, int64_t N, int dtype, int gated, int* rf_nc) {
     const int64_t nblocks = (packed(N, gated) + 15) / 16;
     if (dtype == 0) return plan_f32(M, K, nblocks, gated, rf_nc, rf_nc + 1);
