@@ -72,8 +72,8 @@ KERNEL_SOURCES = {"softmax_pv_deferred": ("softmax_pv.hip", "launch_rules.hpp", 
 _TAKEN_ON = {
     "attention.hip": "cc332201b0474e996589799bda0cedf1acef0142942522b9ae2675ada6a0229b",
     "dn_device.hpp": "7aed1bedca8bd2cd6a906eb0bca1de03527ccb5d1d5a9406e8d4b87a37846ee9",
-    "launch_rules.hpp": "23825b93bd12287e2b8b54f71b5f938aa90c0b8e6ca16f7b570de34219bf0299",
-    "ln_gemm.hip": "b6d7c815d1e885c049b828f62852980ed98cbd906791cf46574b6e285c26d36e",
+    "launch_rules.hpp": "71353aa8d4dd78f7780321d99d79458b8c6ed7fc5be1180429d1b6602ca41680",
+    "ln_gemm.hip": "554b0b390420408f28ba3a96740b79822ceadec766d8d904388b05ee386e5b37",
     "ln_skinny.hip": "4f23350112f84e2f7dc2e0451c02c4d7d0b5dd49472d5d6347d604c0a7352a80",
     "ln_skinny.hpp": "67814d2f1a9f4db68f053b4c82023a7d9ba8567d6e1105c8d7140bba4f66b953",
     "ln_skinny_f32.hip": "2c6d30cdd573ce203e4d88ee7a3890a3e4e86c7790a50bde2175c33499f37a81",
@@ -87,17 +87,17 @@ def _figure(kernel, fetch_kib, fetch_scale, write_kib, write_scale=1.0):
 
 
 TRAFFIC = {(kernel, workload): _figure(kernel, *figures) for kernel, workload, *figures in (
-    ("softmax_pv_deferred", "causal_softmax_pv_bf16_32x8192x8192_d128", 1186058, 1.99992, 65748),
+    ("softmax_pv_deferred", "causal_softmax_pv_bf16_32x8192x8192_d128", 1186077, 1.99992, 65750),
     ("softmax_pv_deferred", "softmax_pv_bf16_12x512x512_d64", 3680, 1.99993, 768),
-    ("ln_linear_deferred", "ln_qkv_bf16_4096x4096x12288", 298954, 1.99994, 109946),
-    ("ln_linear_deferred", "ln_ffn_up_bf16_8192x8192x28672", 2768553, 1.99993, 483157),
-    ("ln_linear_deferred", "ln_ffn_up_bf16_decode_t1_8192x28672", 239504, 1.99994, 56),
+    ("ln_linear_deferred", "ln_qkv_bf16_4096x4096x12288", 298950, 1.99993, 109637),
+    ("ln_linear_deferred", "ln_ffn_up_bf16_8192x8192x28672", 2768551, 1.99993, 481775),
+    ("ln_linear_deferred", "ln_ffn_up_bf16_decode_t1_8192x28672", 239559, 1.99994, 56),
     ("ln_linear_deferred", "ln_linear_f32_128x768x3072", 6230, 1.99993, 1536),
-    ("rms_linear_deferred", "rms_qkv_bf16_4096x4096x6144", 164191, 1.99994, 52479),
+    ("rms_linear_deferred", "rms_qkv_bf16_4096x4096x6144", 164190, 1.99993, 52476),
     ("rms_swiglu_deferred", "rms_swiglu_bf16_decode_t1_8192x28672", 459122, 1.99993, 56),
-    ("attention_deferred", "causal_attention_bf16_32x8192x8192_d128", 247838, 1.99992, 65642),
+    ("attention_deferred", "causal_attention_bf16_32x8192x8192_d128", 249711, 1.99993, 65558),
     # 256 heads fill the chip with one workgroup per head: no key split, no merge kernel
-    ("attention_decode_deferred", "decode_attention_bf16_256x1x8192_d128", 524409, 1.99992, 64),
+    ("attention_decode_deferred", "decode_attention_bf16_256x1x8192_d128", 524411, 1.99992, 64),
 )}
 
 
